@@ -211,6 +211,7 @@ struct Store<LBM_F64> {
   __device__ static __forceinline__ R load(const T *p, int64_t i, float) { return p[i]; }
   __device__ static __forceinline__ void store(T *p, int64_t i, R v, float) { p[i] = v; }
   __device__ static __forceinline__ void store_nt(T *p, int64_t i, R v, float) { __builtin_nontemporal_store(v, p + i); }
+  __device__ static __forceinline__ void put_nt(T *p, T v) { __builtin_nontemporal_store(v, p); }  // stored bits
   // the stored bits as loaded, and their value (the shuffle step moves raw
   // values between lanes and converts each once)
   using Raw = double;
@@ -226,6 +227,7 @@ struct Store<LBM_F32_OFFSET> {
   __device__ static __forceinline__ R load(const T *p, int64_t i, float) { return p[i]; }
   __device__ static __forceinline__ void store(T *p, int64_t i, R v, float) { p[i] = v; }
   __device__ static __forceinline__ void store_nt(T *p, int64_t i, R v, float) { __builtin_nontemporal_store(v, p + i); }
+  __device__ static __forceinline__ void put_nt(T *p, T v) { __builtin_nontemporal_store(v, p); }  // stored bits
   using Raw = float;
   __device__ static __forceinline__ Raw load_raw(const T *p, int64_t i) { return p[i]; }
   __device__ static __forceinline__ R value(Raw r, float) { return r; }

@@ -14,8 +14,8 @@
 // Two v_mbcnt give a region's entry index; regions and the half-way
 // bounce-back (Sec. 3.2: propagation only between non-solid nodes) are merged
 // with v_cndmask on scalar lane masks.  Neighbour records (region offset,
-// node count, fluid mask) come through scalar loads; nothing is staged in LDS
-// and there is no barrier.
+// node count, fluid mask) come through scalar loads; the gather stages nothing
+// in LDS and there is no barrier.
 //
 // Shuffle form (two-copy step only): every lane first loads its own node's
 // 19 post-collision values with coalesced loads (the tile's direction blocks
@@ -137,16 +137,41 @@ constexpr int slot_of(int k) {
   return -1;
 }
 
+// LDS written by this wavefront's lanes is visible to its other lanes (a
+// wavefront's LDS operations take effect in order; no barrier is needed).
+__device__ __forceinline__ void wave_lds_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 constexpr int kTwoCopy = kPhaseTwoCopy, kAAGather = kPhaseAAGather, kAALocal = kPhaseAALocal;
 
-// One 4x4x4 tile: gather, collide, store.  Lanes of solid nodes return
-// early (in the shuffle form SH after the shuffles); every value the
-// wavefront branches on is uniform.
+// LDS bytes in which a wavefront lays out its tile's new values.  Where a step
+// rewrites the nodes' own entries (two copies, and the local step of the
+// single copy), one store per direction would write a run of the tile's
+// non-solid nodes (280 bytes in FP64 at the benchmark's porosity), whose ends
+// share lines with the runs of the directions before and after.  Through LDS
+// the region leaves as 16-byte stores of whole lines, a third of the store
+// instructions.  256^3 spheres, us per step, without / with: FP64 302 / 286,
+// FP32 186 / 180; FP64 cavity of 128^3: 116 / 111.  FP16, whose runs are short
+// and whose step is bound by vector issue, gains 3% there and loses 1% on a
+// 256^3 vessel tree, and stores directly, as the gather/scatter step does,
+// which writes its neighbours' entries.
+template <int S, int PH>
+constexpr int stage_bytes() {
+  return PH == kPhaseAAGather || S == LBM_F16_OFFSET ? 0 : 64 * 19 * (int)sizeof(typename Store<S>::T);
+}
+
+// The nodes of one 4x4x4 tile: gather, collide, store (into `stage`, where
+// there is one).  Lanes of solid nodes return early (in the shuffle form SH
+// after the shuffles); every value the wavefront branches on is uniform.
 template <int S, bool NT, bool INC, int PH, bool MRT, bool SH>
-__device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src_, out_ptr<PH, void> dst_,
-                                            const TileArgs &a, const NbRec *__restrict__ nrec,
-                                            const uint32_t *__restrict__ nrow, const uint32_t *__restrict__ rbase,
-                                            const CollideCoef *__restrict__ coef) {
+__device__ __forceinline__ void step19_nodes(int64_t tile, const NbRec &own, in_ptr<PH, void> src_,
+                                             out_ptr<PH, void> dst_, const TileArgs &a,
+                                             const NbRec *__restrict__ nrec, const uint32_t *__restrict__ nrow,
+                                             const uint32_t *__restrict__ rbase,
+                                             const CollideCoef *__restrict__ coef, char *stage) {
   using L = D3Q19;
   using St = Store<S>;
   using T = typename St::T;
@@ -155,10 +180,9 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src_,
   out_ptr<PH, T> dst = static_cast<T *>(dst_);
   const int lane = threadIdx.x & 63;
 
-  // own record and the 18 neighbour records (empty neighbours point at an
-  // all-solid sentinel record, so every load is unconditional); the local
-  // phase of the single-copy form needs only its own
-  const NbRec own = nrec[tile];
+  // the 18 neighbour records (empty neighbours point at an all-solid sentinel
+  // record, so every load is unconditional); the local phase of the
+  // single-copy form needs only its own
   NbRec nb[PH == kAALocal ? 1 : 18];
   if constexpr (PH != kAALocal)
     static_for<18>([&](auto J) {
@@ -281,18 +305,22 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src_,
   const CollideCoef &cc = coef[own.sample];
   // two-copy: own slot i of the other buffer; single-copy gather: where
   // opp(i) was read; single-copy local: own slot opp(i)
+  const uint32_t nw = (uint32_t)__popcll(M);  // the run of one direction in the staged region
   auto put = [&](auto I, R out) {
     constexpr int i = decltype(I)::value;
-    T *blk;
+    if constexpr (stage_bytes<S, PH>() != 0) {
+      constexpr int slot = PH == kTwoCopy ? i : L::Opp[i];
+      St::store(reinterpret_cast<T *>(stage) + (uint32_t)slot * nw, (int64_t)rank, out, a.f16_scale);
+      return;
+    }
+    T *blk = dst;
     uint32_t e;
     if constexpr (PH == kTwoCopy) {
-      blk = dst + (ooff + (uint32_t)i * on);
+      blk += ooff + (uint32_t)i * on;
       e = rank;
     } else if constexpr (PH == kAAGather) {
-      blk = dst;
       e = ea[L::Opp[i]];
     } else {
-      blk = dst;
       e = ooff + (uint32_t)L::Opp[i] * on + rank;
     }
     if constexpr (NT)
@@ -365,6 +393,42 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src_,
   }
 }
 
+// One 4x4x4 tile.  stage: the wavefront's stage_bytes of LDS, 16-byte aligned.
+template <int S, bool NT, bool INC, int PH, bool MRT, bool SH>
+__device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src, out_ptr<PH, void> dst,
+                                            const TileArgs &a, const NbRec *__restrict__ nrec,
+                                            const uint32_t *__restrict__ nrow, const uint32_t *__restrict__ rbase,
+                                            const CollideCoef *__restrict__ coef, char *stage) {
+  using T = typename Store<S>::T;
+  const NbRec own = nrec[tile];
+  step19_nodes<S, NT, INC, PH, MRT, SH>(tile, own, src, dst, a, nrec, nrow, rbase, coef, stage);
+  if constexpr (stage_bytes<S, PH>() != 0) {
+    const uint32_t lane = threadIdx.x & 63, nw = (uint32_t)__popcll(own.mask);
+    T *region = static_cast<T *>(dst) + own.off;
+    wave_lds_sync();
+    if (nw == own.n) {
+      // the tile's whole region (it starts on a 128-byte boundary and is
+      // padded to one)
+      typedef unsigned v4u __attribute__((ext_vector_type(4)));
+      const uint32_t chunks = (19u * nw * (uint32_t)sizeof(T) + 15u) / 16u;
+      for (uint32_t k = lane; k < chunks; k += 64) {
+        const v4u v = reinterpret_cast<const v4u *>(stage)[k];
+        if constexpr (NT) __builtin_nontemporal_store(v, reinterpret_cast<v4u *>(region) + k);
+        else reinterpret_cast<v4u *>(region)[k] = v;
+      }
+    } else if (lane < nw) {
+      // a 4x4x8 tile's half shares the region with the other half: the runs of
+      // its own nodes, direction by direction
+      for (uint32_t i = 0; i < 19; ++i) {
+        const T v = reinterpret_cast<const T *>(stage)[i * nw + lane];
+        if constexpr (NT) Store<S>::put_nt(region + (i * own.n + lane), v);
+        else region[i * own.n + lane] = v;
+      }
+    }
+    wave_lds_sync();  // a persistent wavefront's next tile uses the same LDS
+  }
+}
+
 // Which tiles a launch visits.
 enum { kDirect = 0, kList = 1, kPersistent = 2 };
 
@@ -378,7 +442,9 @@ __global__ void __launch_bounds__(64 * WPB)
              const uint32_t *__restrict__ nrow, const uint32_t *__restrict__ rbase,
              const CollideCoef *__restrict__ coef, const int32_t *__restrict__ list,
              const int32_t *__restrict__ count) {
+  extern __shared__ __attribute__((aligned(16))) char stage_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  char *stage = stage_lds + wv * stage_bytes<S, PH>();
   // XCD assignment, chosen per form by measurement: chunks of 8 blocks for
   // the two-copy FP64/FP32 step (BGK and MRT), 16 for the FP64 BGK single
   // copy, one contiguous range per XCD for everything else (FP16, the other
@@ -390,14 +456,14 @@ __global__ void __launch_bounds__(64 * WPB)
   const int64_t gw = blk * WPB + wv;
   if constexpr (MODE == kDirect) {
     if (gw >= a.n_waves) return;
-    step19_tile<S, NT, INC, PH, MRT, SH>(gw, src, dst, a, nrec, nrow, rbase, coef);
+    step19_tile<S, NT, INC, PH, MRT, SH>(gw, src, dst, a, nrec, nrow, rbase, coef, stage);
   } else if constexpr (MODE == kList) {
     if (gw >= (int64_t)*count) return;
-    step19_tile<S, NT, INC, PH, MRT, SH>(list[gw], src, dst, a, nrec, nrow, rbase, coef);
+    step19_tile<S, NT, INC, PH, MRT, SH>(list[gw], src, dst, a, nrec, nrow, rbase, coef, stage);
   } else {
     const int64_t n = *count, G = (int64_t)gridDim.x * WPB;
     for (int64_t k = gw; k < n; k += G)
-      step19_tile<S, NT, INC, PH, MRT, SH>(list[k], src, dst, a, nrec, nrow, rbase, coef);
+      step19_tile<S, NT, INC, PH, MRT, SH>(list[k], src, dst, a, nrec, nrow, rbase, coef, stage);
   }
 }
 
@@ -405,6 +471,12 @@ template <int V>
 using IC = std::integral_constant<int, V>;
 template <bool V>
 using BC = std::integral_constant<bool, V>;
+
+// Dynamic LDS above 64 KB (8 wavefronts of FP64) has to be asked for.
+hipError_t allow_lds(const void *kernel, int bytes) {
+  if (bytes <= 65536) return hipSuccess;
+  return hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, bytes);
+}
 
 // Calls f(storage, waves per block, model, phase, MRT, shuffle form) with
 // compile-time constants.  The shuffle form exists for the two-copy step.
@@ -462,7 +534,10 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
     constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
     constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
     auto go = [&](auto kern) {
-      hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * W), 0, s, src, dst, a, nrec, nrow, rbase, coef, list, count);
+      constexpr int lds = W * stage_bytes<S, PH>();
+      const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds);
+      if (e != hipSuccess) return e;
+      hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * W), lds, s, src, dst, a, nrec, nrow, rbase, coef, list, count);
       return hipGetLastError();
     };
     auto by_mode = [&](auto nt) {
@@ -489,9 +564,11 @@ hipError_t step19_persistent_blocks(const Variant &v, bool single_copy, bool shu
     return with_variant(v, phase, shuffle, [&](auto sc, auto wc, auto ic, auto pc, auto mc, auto hc) -> hipError_t {
       constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
       constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
+      constexpr int lds = W * stage_bytes<S, PH>();
+      auto kern = k_step19<S, W, true, INC, PH, MRT, kPersistent, SH>;
       int k = 0;
-      const hipError_t r = hipOccupancyMaxActiveBlocksPerMultiprocessor(
-          &k, k_step19<S, W, true, INC, PH, MRT, kPersistent, SH>, 64 * W, 0);
+      hipError_t r = allow_lds(reinterpret_cast<const void *>(kern), lds);
+      if (r == hipSuccess) r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, kern, 64 * W, lds);
       per = per < 0 ? k : (k < per ? k : per);
       return r;
     });
