@@ -10,12 +10,18 @@
 // with none of them while approaching rho u (T is the identity on smooth
 // fields in the bulk, with eigenvalues in [0, 1]).
 //
+// The sweeps carry the residual r = rho u - j, for which a sweep is
+// r <- r - T r: one field of three components to read at the 18 neighbours
+// instead of rho, u and j, and u = (rho u - r) / rho at the end.
+//
 // Launches on the caller's stream: clear the per-component sums, sum
 // (rho, 1) per component, rescale rho, one stencil launch per sweep
-// (ping-pong buffers in the scratch), then u = j / rho.  Per-component sums
-// use wave-aggregated FP64 atomics: the lanes of a wave that share a label
-// are reduced with cross-lane shuffles and one lane adds the total, so a
-// giant component costs one atomic per wave rather than one per node.
+// (ping-pong buffers in the scratch), the last of which writes u.
+// Per-component sums: a wavefront keeps the component it met first in
+// registers over a stride of nodes and adds any other with cross-lane
+// shuffles, and a workgroup adds one total, so a giant component costs one
+// FP64 atomic pair per workgroup (112 x 104 x 96 at porosity 0.5: 420 -> 16 us
+// against one pair per 64 nodes, all on one address).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -62,16 +68,54 @@ __global__ void __launch_bounds__(kBlock) k_clear(double *p, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = 0.0;
 }
 
+constexpr int kMassBlocks = 256;  // at most one workgroup per compute unit
+
 __global__ void __launch_bounds__(kBlock) k_mass(int64_t n, const int32_t *lab, int32_t count, const double *rho,
                                                  double *acc) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  int L = -1;
-  double r = 0.0;
-  if (i < n) {
-    L = checked(lab[i], count);
-    if (L >= 0) r = rho[i];
+  __shared__ int label_s[kBlock / 64];
+  __shared__ double sum_s[kBlock / 64][2];
+  int cur = -1;  // this wavefront's component (uniform), summed per lane
+  double x = 0.0, y = 0.0;
+  const int64_t first = (blockIdx.x * (int64_t)kBlock + threadIdx.x) & ~(int64_t)63;
+  for (int64_t base = first; base < n; base += (int64_t)gridDim.x * kBlock) {
+    const int64_t i = base + __lane_id();
+    const int L = i < n ? checked(lab[i], count) : -1;
+    const double r = L >= 0 ? rho[i] : 0.0;
+    const unsigned long long any = __ballot(L >= 0);
+    if (cur < 0 && any) cur = __shfl(L, __ffsll(any) - 1);
+    const bool mine = L >= 0 && L == cur;
+    if (mine) {
+      x += r;
+      y += 1.0;
+    }
+    if (__ballot(L >= 0 && !mine)) wave_add2(acc, mine ? -1 : L, r, 1.0);
   }
-  wave_add2(acc, L, r, 1.0);
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    x += __shfl_xor(x, off);
+    y += __shfl_xor(y, off);
+  }
+  const int wv = threadIdx.x >> 6;
+  if (__lane_id() == 0) {
+    label_s[wv] = cur;
+    sum_s[wv][0] = x;
+    sum_s[wv][1] = y;
+  }
+  __syncthreads();
+  if (threadIdx.x != 0) return;
+  for (int w = 0; w < kBlock / 64; ++w) {  // wavefronts of one component are added together
+    const int L = label_s[w];
+    if (L < 0) continue;
+    double a = 0.0, c = 0.0;
+    for (int v = w; v < kBlock / 64; ++v)
+      if (label_s[v] == L) {
+        a += sum_s[v][0];
+        c += sum_s[v][1];
+        if (v > w) label_s[v] = -1;
+      }
+    unsafeAtomicAdd(acc + 2 * (int64_t)L, a);
+    unsafeAtomicAdd(acc + 2 * (int64_t)L + 1, c);
+  }
 }
 
 __global__ void __launch_bounds__(kBlock) k_rescale(int64_t n, const int32_t *lab, int32_t count, const double *acc,
@@ -88,80 +132,148 @@ struct Lattice3 {
   uint32_t periodic;
 };
 
-// j_out = j_in + T(rho u - j_in) on non-solid nodes (0 on solid ones); with
-// j_in == nullptr the sweep starts from j = 0.
-template <class L>
-__global__ void __launch_bounds__(kBlock) k_link_sweep(int64_t n, Lattice3 g, const int32_t *lab, int32_t count,
-                                                       const double *rho, const double *u, const double *j_in,
-                                                       double *j_out) {
-  const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
-  if (i >= n) return;
-  if (checked(lab[i], count) < 0) {
-    j_out[i] = j_out[n + i] = j_out[2 * n + i] = 0.0;
-    return;
-  }
-  const int x = (int)(i % g.nx), y = (int)((i / g.nx) % g.ny), z = (int)(i / ((int64_t)g.nx * g.ny));
-  auto residual = [&](int64_t p, int k) {
-    const double j = j_in ? j_in[k * n + p] : 0.0;
-    return rho[p] * u[k * n + p] - j;
-  };
-  const double r0[3] = {residual(i, 0), residual(i, 1), residual(i, 2)};
-  double acc[3] = {0.0, 0.0, 0.0};
-  lbm::static_for<L::Q>([&](auto d) {
-    constexpr int cx = L::C[d][0], cy = L::C[d][1], cz = L::C[d][2];
-    if constexpr (cx != 0 || cy != 0 || cz != 0) {
-      int tx = x + cx, ty = y + cy, tz = z + cz;
-      bool inside = true;
-      if (tx < 0 || tx >= g.nx) {
-        inside &= (g.periodic & 1u) != 0;
-        tx = tx < 0 ? tx + g.nx : tx - g.nx;
-      }
-      if (ty < 0 || ty >= g.ny) {
-        inside &= (g.periodic & 2u) != 0;
-        ty = ty < 0 ? ty + g.ny : ty - g.ny;
-      }
-      if (tz < 0 || tz >= g.nz) {
-        inside &= (g.periodic & 4u) != 0;
-        tz = tz < 0 ? tz + g.nz : tz - g.nz;
-      }
-      if (inside) {
-        const int64_t t = (int64_t)tx + (int64_t)g.nx * ((int64_t)ty + (int64_t)g.ny * tz);
-        if (checked(lab[t], count) >= 0) {
-          double s = 0.0;
-          if constexpr (cx != 0) s += cx * (r0[0] + residual(t, 0));
-          if constexpr (cy != 0) s += cy * (r0[1] + residual(t, 1));
-          if constexpr (cz != 0) s += cz * (r0[2] + residual(t, 2));
-          s *= 1.5 * L::Wt[d];
-          if constexpr (cx != 0) acc[0] += cx * s;
-          if constexpr (cy != 0) acc[1] += cy * s;
-          if constexpr (cz != 0) acc[2] += cz * s;
-        }
-      }
+// One sweep on bricks of 16x8x8 nodes: the brick's residuals and those of the
+// nodes around it go to LDS once (0 on solid nodes, so they add nothing as
+// neighbours), with a bit per node for "non-solid" in one word per x-row, and
+// each thread computes four nodes from there.  With s the sum over the links
+// to non-solid neighbours,
+//   T r(x) = 3/2 s w c (c.r(x + c)) + 3/2 (s w c c^T) r(x):
+// the first part needs no masks, the second only counts of open links.
+// What bounds it: 48 LDS reads per node; 112 x 104 x 96 nodes take 28 us per
+// sweep, against 58-85 us for the form that read rho, u and j of every
+// neighbour from memory.
+constexpr int kSx = 16, kSy = 8, kSz = 8;
+constexpr int kHx = kSx + 2, kHy = kSy + 2, kHz = kSz + 2, kHaloNodes = kHx * kHy * kHz;
+static_assert(kSx * kSy * kSz == 4 * kBlock && kHx <= 32, "four nodes per thread, a row's bits in one word");
+
+// What a sweep reads and writes: the first one takes r = rho u from the
+// fields; the last one writes u.
+enum SweepEnds : int { kInner = 0, kFirst = 1, kLast = 2 };
+
+// rho u, rounded once where r starts and where u is formed, so that a node no
+// link reaches (r = rho u to the end) comes out at rest exactly
+__device__ __forceinline__ double momentum(double rho, double u) { return __dmul_rn(rho, u); }
+
+template <class L, int ENDS>
+__global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t *lab, int32_t count,
+                                                       const double *rho, double *u, const double *r_in,
+                                                       double *r_out) {
+  __shared__ double rs[3][kHaloNodes];
+  __shared__ uint32_t open[kHy * kHz];
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
+  const int tid = threadIdx.x;
+  const int bx = (g.nx + kSx - 1) / kSx, by = (g.ny + kSy - 1) / kSy;
+  const int ox = (int)(blockIdx.x % bx) * kSx, oy = (int)(blockIdx.x / bx % by) * kSy,
+            oz = (int)(blockIdx.x / ((unsigned)bx * by)) * kSz;
+  if (tid < kHy * kHz) open[tid] = 0;
+  __syncthreads();
+  for (int e = tid; e < kHaloNodes; e += kBlock) {
+    const int hx = e % kHx, row = e / kHx;
+    int t[3] = {ox + hx - 1, oy + row % kHy - 1, oz + row / kHy - 1};
+    const int ext[3] = {g.nx, g.ny, g.nz};
+    bool inside = true;
+    for (int a = 0; a < 3; ++a) {
+      // one node beyond a face is across it or outside; further out (past a
+      // ragged brick's end) is read by no node of the lattice
+      const bool over = t[a] < 0 || t[a] >= ext[a];
+      inside = inside && (!over || (((g.periodic >> a) & 1u) && t[a] <= ext[a]));
+      if (over) t[a] = t[a] < 0 ? ext[a] - 1 : 0;
     }
-  });
-  for (int k = 0; k < 3; ++k) j_out[k * n + i] = (j_in ? j_in[k * n + i] : 0.0) + acc[k];
+    double r[3] = {0.0, 0.0, 0.0};
+    const int64_t p = (int64_t)t[0] + (int64_t)g.nx * ((int64_t)t[1] + (int64_t)g.ny * t[2]);
+    if (inside && checked(lab[p], count) >= 0) {
+      if constexpr (ENDS & kFirst) {
+        const double m = rho[p];
+        for (int k = 0; k < 3; ++k) r[k] = momentum(m, u[k * n + p]);
+      } else {
+        for (int k = 0; k < 3; ++k) r[k] = r_in[k * n + p];
+      }
+      atomicOr(&open[row], 1u << hx);
+    }
+    for (int k = 0; k < 3; ++k) rs[k][e] = r[k];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const int lx = tid % kSx, ly = tid / kSx % kSy, lz = tid / (kSx * kSy) + q * (kSz / 4);
+    const int x = ox + lx, y = oy + ly, z = oz + lz;
+    if (x >= g.nx || y >= g.ny || z >= g.nz) continue;
+    const int c0 = lx + 1 + kHx * (ly + 1 + kHy * (lz + 1)), row0 = ly + 1 + kHy * (lz + 1);
+    const int64_t i = (int64_t)x + (int64_t)g.nx * ((int64_t)y + (int64_t)g.ny * z);
+    if (!((open[row0] >> (lx + 1)) & 1u)) {
+      if constexpr (!(ENDS & kLast))
+        for (int k = 0; k < 3; ++k) r_out[k * n + i] = 0.0;
+      continue;
+    }
+    const double r0[3] = {rs[0][c0], rs[1][c0], rs[2][c0]};
+    double acc[3] = {0.0, 0.0, 0.0};  // 2/3 T r, weight by weight
+    lbm::static_for<2>([&](auto Cls) {
+      constexpr bool edge = decltype(Cls)::value == 1;  // links with two nonzero components, or one
+      double s[3] = {0.0, 0.0, 0.0};
+      int diag[3] = {0, 0, 0}, off[3] = {0, 0, 0};  // counts of c_a c_a, and of c_a c_b for ab = yz, xz, xy
+      lbm::static_for<L::Q>([&](auto d) {
+        constexpr int cx = L::C[d][0], cy = L::C[d][1], cz = L::C[d][2];
+        constexpr int nz = (cx != 0) + (cy != 0) + (cz != 0);
+        if constexpr (nz == (edge ? 2 : 1)) {
+          const int t = c0 + cx + kHx * (cy + kHy * cz);
+          double v = 0.0;
+          if constexpr (cx != 0) v += cx * rs[0][t];
+          if constexpr (cy != 0) v += cy * rs[1][t];
+          if constexpr (cz != 0) v += cz * rs[2][t];
+          if constexpr (cx != 0) s[0] += cx * v;
+          if constexpr (cy != 0) s[1] += cy * v;
+          if constexpr (cz != 0) s[2] += cz * v;
+          const int b = (int)((open[row0 + cy + kHy * cz] >> (lx + 1 + cx)) & 1u);
+          if constexpr (cx != 0) diag[0] += b;
+          if constexpr (cy != 0) diag[1] += b;
+          if constexpr (cz != 0) diag[2] += b;
+          if constexpr (cy * cz != 0) off[0] += cy * cz * b;
+          if constexpr (cx * cz != 0) off[1] += cx * cz * b;
+          if constexpr (cx * cy != 0) off[2] += cx * cy * b;
+        }
+      });
+      s[0] += diag[0] * r0[0] + off[2] * r0[1] + off[1] * r0[2];
+      s[1] += off[2] * r0[0] + diag[1] * r0[1] + off[0] * r0[2];
+      s[2] += off[1] * r0[0] + off[0] * r0[1] + diag[2] * r0[2];
+      constexpr double w = 1.5 * L::Wt[edge ? L::Q - 1 : 1];
+      for (int k = 0; k < 3; ++k) acc[k] += w * s[k];
+    });
+    if constexpr (ENDS & kLast) {
+      const double m = rho[i];
+      for (int k = 0; k < 3; ++k) u[k * n + i] = (momentum(m, u[k * n + i]) - (r0[k] - acc[k])) / m;
+    } else {
+      for (int k = 0; k < 3; ++k) r_out[k * n + i] = r0[k] - acc[k];
+    }
+  }
 }
 
+// u = (rho u - r) / rho after a single sweep (which reads its neighbours' u)
 __global__ void __launch_bounds__(kBlock) k_velocity(int64_t n, const int32_t *lab, int32_t count, const double *rho,
-                                                     const double *j, double *u) {
+                                                     const double *r, double *u) {
   const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i >= n || checked(lab[i], count) < 0) return;
-  const double r = rho[i];
-  for (int k = 0; k < 3; ++k) u[k * n + i] = j[k * n + i] / r;
+  const double m = rho[i];
+  for (int k = 0; k < 3; ++k) u[k * n + i] = (momentum(m, u[k * n + i]) - r[k * n + i]) / m;
 }
 
 template <class L>
-void launch_sweeps(int64_t n, Lattice3 g, const int32_t *labels, int32_t count, const double *rho, const double *u,
-                   double *ja, double *jb, int iterations, hipStream_t s, const double **final_j) {
-  const unsigned grid = (unsigned)((n + kBlock - 1) / kBlock);
-  const double *in = nullptr;
-  double *out = ja;
-  for (int it = 0; it < iterations; ++it) {
-    hipLaunchKernelGGL(k_link_sweep<L>, dim3(grid), dim3(kBlock), 0, s, n, g, labels, count, rho, u, in, out);
-    in = out;
-    out = out == ja ? jb : ja;
+void launch_sweeps(int64_t n, Lattice3 g, const int32_t *labels, int32_t count, const double *rho, double *u,
+                   double *ra, double *rb, int iterations, hipStream_t s) {
+  const int64_t bricks =
+      (int64_t)((g.nx + kSx - 1) / kSx) * ((g.ny + kSy - 1) / kSy) * ((g.nz + kSz - 1) / kSz);
+  const dim3 grid((unsigned)bricks), block(kBlock);
+  hipLaunchKernelGGL((k_link_sweep<L, kFirst>), grid, block, 0, s, g, labels, count, rho, u, (const double *)nullptr,
+                     ra);
+  if (iterations == 1) {
+    hipLaunchKernelGGL(k_velocity, dim3((unsigned)((n + kBlock - 1) / kBlock)), block, 0, s, n, labels, count, rho,
+                       (const double *)ra, u);
+    return;
   }
-  *final_j = in;
+  for (int it = 1; it + 1 < iterations; ++it) {
+    hipLaunchKernelGGL((k_link_sweep<L, kInner>), grid, block, 0, s, g, labels, count, rho, u, (const double *)ra, rb);
+    std::swap(ra, rb);
+  }
+  hipLaunchKernelGGL((k_link_sweep<L, kLast>), grid, block, 0, s, g, labels, count, rho, u, (const double *)ra, rb);
 }
 
 }  // namespace
@@ -188,17 +300,16 @@ extern "C" int lbm_project_invariants(int32_t q, const int32_t shape[3], uint32_
   const int64_t sums = 2 * (int64_t)count;
   const unsigned clear_grid = (unsigned)std::min<int64_t>((sums + kBlock - 1) / kBlock, 4096);
   double *acc = scratch;
-  double *ja = scratch + sums, *jb = ja + 3 * n;
+  double *ra = scratch + sums, *rb = ra + 3 * n;
   hipLaunchKernelGGL(k_clear, dim3(clear_grid), dim3(kBlock), 0, s, acc, sums);
-  hipLaunchKernelGGL(k_mass, dim3(grid), dim3(kBlock), 0, s, n, labels, count, (const double *)rho, acc);
+  hipLaunchKernelGGL(k_mass, dim3(std::min<unsigned>(grid, kMassBlocks)), dim3(kBlock), 0, s, n, labels, count,
+                     (const double *)rho, acc);
   hipLaunchKernelGGL(k_rescale, dim3(grid), dim3(kBlock), 0, s, n, labels, count, (const double *)acc, rho0, rho);
   const Lattice3 g{shape[0], shape[1], shape[2], periodic};
-  const double *j = nullptr;
   if (q == 19)
-    launch_sweeps<lbm::D3Q19>(n, g, labels, count, rho, u, ja, jb, iterations, s, &j);
+    launch_sweeps<lbm::D3Q19>(n, g, labels, count, rho, u, ra, rb, iterations, s);
   else
-    launch_sweeps<lbm::D2Q9>(n, g, labels, count, rho, u, ja, jb, iterations, s, &j);
-  hipLaunchKernelGGL(k_velocity, dim3(grid), dim3(kBlock), 0, s, n, labels, count, (const double *)rho, j, u);
+    launch_sweeps<lbm::D2Q9>(n, g, labels, count, rho, u, ra, rb, iterations, s);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return set_error(LBM_ERR_HIP, "lbm_project_invariants: %s", hipGetErrorString(e));
   return LBM_OK;
@@ -244,8 +355,37 @@ struct CcGrid {
   int nx, ny, nz;
 };
 
+// Joins the trees of nodes e and f.
+__device__ __forceinline__ void cc_join(int32_t *parent, int32_t e, int32_t f) {
+  int32_t a = cc_find(parent, e), b = cc_find(parent, f);
+  while (a != b) {
+    if (a > b) {
+      const int32_t s = a;
+      a = b;
+      b = s;
+    }
+    const int32_t old = atomicCAS(parent + b, b, a);
+    if (old == b) break;  // b now hangs under a
+    b = cc_find(parent, old);
+    a = cc_find(parent, a);
+  }
+}
+
+// The node one link c away from (x, y, z), or -1 past an edge that does not wrap.
+__device__ __forceinline__ int64_t cc_link(const CcGrid &g, uint32_t periodic, int x, int y, int z, int cx, int cy,
+                                           int cz) {
+  int t[3] = {x + cx, y + cy, z + cz};
+  const int ext[3] = {g.nx, g.ny, g.nz};
+  for (int a = 0; a < 3; ++a) {
+    if (t[a] >= 0 && t[a] < ext[a]) continue;
+    if (!((periodic >> a) & 1u)) return -1;
+    t[a] = t[a] < 0 ? t[a] + ext[a] : t[a] - ext[a];
+  }
+  return (int64_t)t[0] + (int64_t)g.nx * ((int64_t)t[1] + (int64_t)g.ny * t[2]);
+}
+
 // One thread per node: union with the non-solid node one link away, for one
-// link of each opposite pair (only links with c_axis != 0 when axis >= 0).
+// link of each opposite pair, only links with c_axis != 0.
 template <class L>
 __global__ void __launch_bounds__(kBlock) k_cc_union(CcGrid g, uint32_t periodic, int axis, const uint8_t *solid,
                                                      int32_t *parent) {
@@ -257,29 +397,60 @@ __global__ void __launch_bounds__(kBlock) k_cc_union(CcGrid g, uint32_t periodic
     constexpr int i = decltype(I)::value;
     constexpr int cx = L::C[i][0], cy = L::C[i][1], cz = L::C[i][2];
     if constexpr ((cx != 0 || cy != 0 || cz != 0) && i < L::Opp[i]) {
-      const int c[3] = {cx, cy, cz};
-      if (axis >= 0 && c[axis] == 0) return;
-      int t[3] = {x + cx, y + cy, z + cz};
-      const int ext[3] = {g.nx, g.ny, g.nz};
-      for (int a = 0; a < 3; ++a) {
-        if (t[a] >= 0 && t[a] < ext[a]) continue;
-        if (!((periodic >> a) & 1u)) return;
-        t[a] = t[a] < 0 ? t[a] + ext[a] : t[a] - ext[a];
+      if ((axis == 0 ? cx : axis == 1 ? cy : cz) == 0) return;
+      const int64_t f = cc_link(g, periodic, x, y, z, cx, cy, cz);
+      if (f >= 0 && !solid[f]) cc_join(parent, (int32_t)e, (int32_t)f);
+    }
+  });
+}
+
+// With every link (axis = -1) most unions say what others already do, so the
+// links are thinned first.  k_cc_runs hangs each node under the first node of
+// its x-run inside its wavefront's 64 nodes (one ballot, no search).  Then
+//   - an x-link joins only where a run crosses a wavefront's start or wraps;
+//   - a link with c_x = 0 whose copy one node to the left exists is implied by
+//     it (both ends are joined to their left neighbours by x-links);
+//   - a diagonal link is implied where either of its two corners is non-solid.
+// 128^3 at porosity 0.5: 530-600 us for nine unions per node, 134-144 us so.
+__global__ void __launch_bounds__(kBlock) k_cc_runs(CcGrid g, const uint8_t *solid, int32_t *parent) {
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const bool fluid = e < n && !solid[e];
+  const uint64_t open = __ballot(fluid), edge = __ballot(e % g.nx == 0);
+  const uint64_t starts = open & (~(open << 1) | edge);  // (lane 0: nothing to its left in this wavefront)
+  if (e >= n) return;
+  const int lane = __lane_id();
+  const int first = 63 - __clzll((long long)(starts & (~0ull >> (63 - lane))));
+  parent[e] = fluid ? (int32_t)(e - lane + first) : -1;
+}
+
+template <class L>
+__global__ void __launch_bounds__(kBlock) k_cc_union_all(CcGrid g, uint32_t periodic, const uint8_t *solid,
+                                                         int32_t *parent) {
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
+  const int64_t e = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (e >= n || solid[e]) return;
+  const int x = (int)(e % g.nx), y = (int)((e / g.nx) % g.ny), z = (int)(e / ((int64_t)g.nx * g.ny));
+  const bool left = x > 0 && !solid[e - 1];
+  auto open = [&](int cx, int cy, int cz) {
+    const int64_t f = cc_link(g, periodic, x, y, z, cx, cy, cz);
+    return f >= 0 && !solid[f];
+  };
+  lbm::static_for<L::Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    constexpr int cx = L::C[i][0], cy = L::C[i][1], cz = L::C[i][2];
+    if constexpr ((cx != 0 || cy != 0 || cz != 0) && i < L::Opp[i]) {
+      if constexpr (cx != 0 && cy == 0 && cz == 0)
+        if (x + 1 < g.nx && ((e + 1) & 63) != 0) return;  // one run of one wavefront
+      const int64_t f = cc_link(g, periodic, x, y, z, cx, cy, cz);
+      if (f < 0 || solid[f]) return;
+      if constexpr (cx == 0)
+        if (left && !solid[f - 1]) return;
+      if constexpr ((cx != 0) + (cy != 0) + (cz != 0) == 2) {
+        if (open(cx, cx != 0 ? 0 : cy, 0)) return;
+        if (open(0, cx != 0 ? cy : 0, cz)) return;
       }
-      const int64_t f = (int64_t)t[0] + (int64_t)g.nx * ((int64_t)t[1] + (int64_t)g.ny * t[2]);
-      if (solid[f]) return;
-      int32_t a = cc_find(parent, (int32_t)e), b = cc_find(parent, (int32_t)f);
-      while (a != b) {
-        if (a > b) {
-          const int32_t s = a;
-          a = b;
-          b = s;
-        }
-        const int32_t old = atomicCAS(parent + b, b, a);
-        if (old == b) break;  // b now hangs under a
-        b = cc_find(parent, old);
-        a = cc_find(parent, a);
-      }
+      cc_join(parent, (int32_t)e, (int32_t)f);
     }
   });
 }
@@ -387,12 +558,20 @@ int components_device(const char *who, int32_t q, const uint8_t *solid, const in
   const CcGrid g{shape[0], shape[1], shape[2]};
   const int64_t per = (int64_t)kScanBlock * kScanItems, nb = (n + per - 1) / per;
   int32_t *flag = scratch, *sums = scratch + n;
-  hipLaunchKernelGGL(k_cc_init, dim3(cc_grid(n)), dim3(kBlock), 0, s, n, solid, labels);
   const unsigned all = (unsigned)((n + kBlock - 1) / kBlock);
-  if (q == 19)
-    hipLaunchKernelGGL(k_cc_union<lbm::D3Q19>, dim3(all), dim3(kBlock), 0, s, g, periodic, axis, solid, labels);
-  else
-    hipLaunchKernelGGL(k_cc_union<lbm::D2Q9>, dim3(all), dim3(kBlock), 0, s, g, periodic, axis, solid, labels);
+  if (axis < 0) {
+    hipLaunchKernelGGL(k_cc_runs, dim3(all), dim3(kBlock), 0, s, g, solid, labels);
+    if (q == 19)
+      hipLaunchKernelGGL(k_cc_union_all<lbm::D3Q19>, dim3(all), dim3(kBlock), 0, s, g, periodic, solid, labels);
+    else
+      hipLaunchKernelGGL(k_cc_union_all<lbm::D2Q9>, dim3(all), dim3(kBlock), 0, s, g, periodic, solid, labels);
+  } else {
+    hipLaunchKernelGGL(k_cc_init, dim3(cc_grid(n)), dim3(kBlock), 0, s, n, solid, labels);
+    if (q == 19)
+      hipLaunchKernelGGL(k_cc_union<lbm::D3Q19>, dim3(all), dim3(kBlock), 0, s, g, periodic, axis, solid, labels);
+    else
+      hipLaunchKernelGGL(k_cc_union<lbm::D2Q9>, dim3(all), dim3(kBlock), 0, s, g, periodic, axis, solid, labels);
+  }
   hipLaunchKernelGGL(k_cc_flatten, dim3(cc_grid(n)), dim3(kBlock), 0, s, n, labels, flag);
   hipLaunchKernelGGL(k_scan_block, dim3((unsigned)nb), dim3(kScanBlock), 0, s, n, flag, sums);
   hipLaunchKernelGGL(k_scan_sums, dim3(1), dim3(kScanBlock), 0, s, nb, sums);
