@@ -8,6 +8,7 @@
 // is one 16-byte load of 8 consecutive channels.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <initializer_list>
 
@@ -1523,39 +1524,166 @@ __global__ void k_dist_init(int64_t n, const uint8_t *solid, float *d) {
     d[e] = solid[e] ? 0.f : kFar;
 }
 
-__global__ void __launch_bounds__(256) k_dist_sweep(Grid g, uint32_t periodic, const uint8_t *solid,
-                                                    const float *din, float *dout) {
-  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
-  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (e >= n) return;
-  if (solid[e]) {
-    dout[e] = 0.f;
+// Four sweeps per launch on bricks of at most 16^3 nodes: the brick and the
+// four nodes around it go to LDS, where the sweeps run; the outermost layer is
+// left as it is, so what is wrong moves in by one node a sweep and stops at
+// the brick.  Each sweep reads every value before it writes any (the results
+// are those of sweeps over the whole grid, bit for bit, whatever their count).
+// A thread owns four nodes in x of six z-layers and marches up z: a layer's
+// nodes are read once (nine 4-node reads per layer), for the minimum over the
+// layer itself and for what it offers to the layers above and below.
+// A brick whose own and neighbouring values did not change in the launch
+// before is done: it keeps its values (both buffers hold them).  The sign bit
+// of its first value carries "changed" to the next launch; the last launch
+// clears it.  128^3 at porosity 0.5, 64 sweeps: 1770 us for one launch per
+// sweep (27 us each, 18 neighbour loads per node), 390 us so (77 us a launch
+// while most bricks change, bound by vector instructions; 5 us once all are
+// done).
+constexpr int kDistSweeps = 4, kDistBrick = 16, kDistRegion = kDistBrick + 2 * kDistSweeps;  // 24
+constexpr int kDistLayers = 6;
+constexpr int kDistThreads = kDistRegion / 4 * kDistRegion * (kDistRegion / kDistLayers);  // 576
+
+// Bricks of an axis: n split into ceil(n / 16) pieces of nearly equal length
+// (at least 8 where there is more than one, so a halo of 4 ends in the next).
+__device__ __forceinline__ int dist_bricks(int n) { return (n + kDistBrick - 1) / kDistBrick; }
+__device__ __forceinline__ int dist_begin(int b, int n) {
+  const int nb = dist_bricks(n), rem = n % nb;
+  return b * (n / nb) + (b < rem ? b : rem);
+}
+
+__global__ void __launch_bounds__(kDistThreads, 5)
+    k_dist_sweeps(Grid g, uint32_t periodic, const uint8_t *solid, const float *din, float *dout, int sweeps, int skip,
+                  int last) {
+  // one layer, one row and one node of padding at either end: the outermost
+  // nodes' reads past the region stay in the array (what they give reaches
+  // only values that are not kept), so every read is a constant offset away
+  constexpr int kRow = kDistRegion, kLayer = kDistRegion * kDistRegion, kPad = (kLayer + kRow + 1 + 7) / 8 * 8;
+  __shared__ __attribute__((aligned(16))) float d_s[kPad + kDistRegion * kLayer + kPad];
+  __shared__ int busy;
+  float *const d = d_s + kPad;
+  const int n[3] = {g.nx, g.ny, g.nz};
+  const int nb[3] = {dist_bricks(g.nx), dist_bricks(g.ny), dist_bricks(g.nz)};
+  const int blk[3] = {(int)(blockIdx.x % nb[0]), (int)(blockIdx.x / nb[0] % nb[1]),
+                      (int)(blockIdx.x / ((unsigned)nb[0] * nb[1]))};
+  int o[3], len[3];  // the brick
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    o[a] = dist_begin(blk[a], n[a]);
+    len[a] = dist_begin(blk[a] + 1, n[a]) - o[a];
+  }
+  const int tid = threadIdx.x;
+  const int64_t corner = vidx(o[0], o[1], o[2], g);
+  if (tid == 0) busy = !skip;
+  __syncthreads();
+  if (skip && tid < 27) {
+    int q[3] = {blk[0] + tid % 3 - 1, blk[1] + tid / 3 % 3 - 1, blk[2] + tid / 9 - 1};
+    bool there = true;
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      if (q[a] < 0 || q[a] >= nb[a]) {
+        there = there && ((periodic >> a) & 1u);
+        q[a] = q[a] < 0 ? nb[a] - 1 : 0;
+      }
+    if (there && signbit(din[vidx(dist_begin(q[0], n[0]), dist_begin(q[1], n[1]), dist_begin(q[2], n[2]), g)]))
+      busy = 1;
+  }
+  __syncthreads();
+  if (!busy) {
+    if (tid == 0) dout[corner] = fabsf(din[corner]);
     return;
   }
-  const int x = (int)(e % g.nx), y = (int)((e / g.nx) % g.ny), z = (int)(e / ((int64_t)g.nx * g.ny));
-  float best = din[e];
-  lbm::static_for<19>([&](auto i) {
-    constexpr int cx = lbm::D3Q19::C[i][0], cy = lbm::D3Q19::C[i][1], cz = lbm::D3Q19::C[i][2];
-    if constexpr (cx != 0 || cy != 0 || cz != 0) {
-      constexpr float len = ((cx != 0) + (cy != 0) + (cz != 0)) == 1 ? 1.0f : 1.41421356237309515f;
-      int tx = x + cx, ty = y + cy, tz = z + cz;
-      bool inside = true;
-      if (tx < 0 || tx >= g.nx) {
-        inside &= (periodic & 1u) != 0;
-        tx = tx < 0 ? tx + g.nx : tx - g.nx;
-      }
-      if (ty < 0 || ty >= g.ny) {
-        inside &= (periodic & 2u) != 0;
-        ty = ty < 0 ? ty + g.ny : ty - g.ny;
-      }
-      if (tz < 0 || tz >= g.nz) {
-        inside &= (periodic & 4u) != 0;
-        tz = tz < 0 ? tz + g.nz : tz - g.nz;
-      }
-      if (inside) best = fminf(best, din[vidx(tx, ty, tz, g)] + len);
+  // a region coordinate's node along an axis (wrapped), -1 past a wall
+  auto node = [&](int a, int l) -> int {
+    int v = o[a] - kDistSweeps + l;
+    if (v >= 0 && v < n[a]) return v;
+    if (!((periodic >> a) & 1u)) return -1;
+    v %= n[a];
+    return v < 0 ? v + n[a] : v;
+  };
+#pragma unroll 4
+  for (int e = tid; e < kDistRegion * kDistRegion * kDistRegion; e += kDistThreads) {
+    const int x = node(0, e % kDistRegion), y = node(1, e / kDistRegion % kDistRegion),
+              z = node(2, e / (kDistRegion * kDistRegion));
+    float v = kFar;
+    if (x >= 0 && y >= 0 && z >= 0) {
+      const int64_t i = vidx(x, y, z, g);
+      v = din ? fabsf(din[i]) : (solid[i] ? 0.f : kFar);
     }
-  });
-  dout[e] = best;
+    d[e] = v;
+  }
+  __syncthreads();
+  const int x0 = 4 * (tid % (kDistRegion / 4)), y = tid / (kDistRegion / 4) % kDistRegion,
+            z0 = kDistLayers * (tid / (kDistRegion / 4 * kDistRegion));
+  // nodes this thread may change: inside the region's outermost layer and the walls
+  bool xy_ok[4], z_ok[kDistLayers];
+  auto free = [&](int a, int l) {
+    const int v = o[a] - kDistSweeps + l;
+    return l > 0 && l < kDistRegion - 1 && (((periodic >> a) & 1u) || (v >= 0 && v < n[a]));
+  };
+#pragma unroll
+  for (int k = 0; k < 4; ++k) xy_ok[k] = free(0, x0 + k) && free(1, y);
+#pragma unroll
+  for (int l = 0; l < kDistLayers; ++l) z_ok[l] = free(2, z0 + l);
+  float *const mine = d + x0 + kRow * y + kLayer * z0;
+  constexpr float kDiag = 1.41421356237309515f;
+  // nodes whose change makes the brick (and so its neighbours) work on
+  bool x_in[4], z_in[kDistLayers];
+#pragma unroll
+  for (int k = 0; k < 4; ++k)
+    x_in[k] = x0 + k >= kDistSweeps && x0 + k < kDistSweeps + len[0] && y >= kDistSweeps && y < kDistSweeps + len[1];
+#pragma unroll
+  for (int l = 0; l < kDistLayers; ++l) z_in[l] = z0 + l >= kDistSweeps && z0 + l < kDistSweeps + len[2];
+  // distances are not negative, so they order as their bits do (and the
+  // minimum of integers needs no care for signalling NaNs)
+  auto lower = [](float a, float b) {
+    return __uint_as_float(min(__float_as_uint(a), __float_as_uint(b)));
+  };
+  bool changed = false;
+  for (int s = 0; s < sweeps; ++s) {
+    // offered by the layer below; the layer's own minimum and its old values
+    float fresh[kDistLayers][4], below[4], here[4], old[4];
+#pragma unroll
+    for (int l = -1; l <= kDistLayers; ++l) {
+      float row[3][6];
+#pragma unroll
+      for (int r = 0; r < 3; ++r) {
+        const float *p = mine + kLayer * l + kRow * (r - 1);
+        const float4 m = *reinterpret_cast<const float4 *>(p);
+        row[r][0] = p[-1];
+        row[r][1] = m.x, row[r][2] = m.y, row[r][3] = m.z, row[r][4] = m.w;
+        row[r][5] = p[4];
+      }
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const float c = row[1][k + 1];
+        const float face = lower(lower(row[1][k], row[1][k + 2]), lower(row[0][k + 1], row[2][k + 1]));
+        const float diag = lower(lower(row[0][k], row[0][k + 2]), lower(row[2][k], row[2][k + 2]));
+        const float offer = lower(c + 1.f, face + kDiag);
+        if (l > 0) {
+          const bool ok = z_ok[l - 1] && xy_ok[k];
+          fresh[l - 1][k] = ok ? lower(here[k], offer) : old[k];
+          changed |= fresh[l - 1][k] < old[k] && z_in[l - 1] && x_in[k];
+        }
+        if (l >= 0 && l < kDistLayers) here[k] = lower(lower(c, below[k]), lower(face + 1.f, diag + kDiag));
+        below[k] = offer;
+        old[k] = c;
+      }
+      __builtin_amdgcn_sched_barrier(0);  // a layer's reads at a time: all of them at once would spill
+    }
+    __syncthreads();  // every read of this sweep is done
+#pragma unroll
+    for (int l = 0; l < kDistLayers; ++l)
+      *reinterpret_cast<float4 *>(mine + kLayer * l) =
+          make_float4(fresh[l][0], fresh[l][1], fresh[l][2], fresh[l][3]);
+    __syncthreads();
+  }
+  const bool mark = __syncthreads_or(changed || !din) && !last;
+  for (int e = tid; e < len[0] * len[1] * len[2]; e += kDistThreads) {
+    const int x = e % len[0], yy = e / len[0] % len[1], z = e / (len[0] * len[1]);
+    float v = d[x + kDistSweeps + kRow * (yy + kDistSweeps) + kLayer * (z + kDistSweeps)];
+    if (mark && e == 0) v = -v;
+    dout[vidx(o[0] + x, o[1] + yy, o[2] + z, g)] = v;
+  }
 }
 
 // x row = (solid, s, s^2, 0, ...) with s = min(d * scale, cap) on non-solid nodes
@@ -2285,11 +2413,16 @@ extern "C" int lbm_nn_distance(const int32_t shape[3], uint32_t periodic, const 
   const Grid g{shape[0], shape[1], shape[2]};
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  hipLaunchKernelGGL(k_dist_init, dim3(grid_for(n)), dim3(256), 0, s, n, solid, dist);
-  const unsigned grid = (unsigned)((n + 255) / 256);
-  for (int k = 0; k < (sweeps + 1) / 2; ++k) {  // pairs of sweeps end in dist
-    hipLaunchKernelGGL(k_dist_sweep, dim3(grid), dim3(256), 0, s, g, periodic, solid, (const float *)dist, tmp);
-    hipLaunchKernelGGL(k_dist_sweep, dim3(grid), dim3(256), 0, s, g, periodic, solid, (const float *)tmp, dist);
+  if (sweeps == 0) hipLaunchKernelGGL(k_dist_init, dim3(grid_for(n)), dim3(256), 0, s, n, solid, dist);
+  auto bricks = [](int v) { return (int64_t)((v + kDistBrick - 1) / kDistBrick); };
+  const unsigned grid = (unsigned)(bricks(g.nx) * bricks(g.ny) * bricks(g.nz));
+  // pairs of sweeps, four to a launch; the last launch ends in dist
+  const int total = (sweeps + 1) / 2 * 2, launches = (total + kDistSweeps - 1) / kDistSweeps;
+  for (int k = 0; k < launches; ++k) {
+    float *out = (launches - k) % 2 ? dist : tmp;
+    const float *in = k == 0 ? nullptr : (out == dist ? tmp : dist);
+    hipLaunchKernelGGL(k_dist_sweeps, dim3(grid), dim3(kDistThreads), 0, s, g, periodic, solid, in, out,
+                       std::min(kDistSweeps, total - kDistSweeps * k), k >= 2 ? 1 : 0, k + 1 == launches ? 1 : 0);
   }
   NN_TRY(hipGetLastError());
   return LBM_OK;
