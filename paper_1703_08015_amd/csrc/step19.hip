@@ -156,11 +156,14 @@ constexpr int kTwoCopy = kPhaseTwoCopy, kAAGather = kPhaseAAGather, kAALocal = k
 // instructions.  256^3 spheres, us per step, without / with: FP64 302 / 286,
 // FP32 186 / 180; FP64 cavity of 128^3: 116 / 111.  FP16, whose runs are short
 // and whose step is bound by vector issue, gains 3% there and loses 1% on a
-// 256^3 vessel tree, and stores directly, as the gather/scatter step does,
-// which writes its neighbours' entries.
-template <int S, int PH>
+// 256^3 vessel tree, and stores directly, as does FP32 with the MRT collision
+// (2% slower staged) and the gather/scatter step, which writes its neighbours'
+// entries.
+template <int S, int PH, bool MRT>
 constexpr int stage_bytes() {
-  return PH == kPhaseAAGather || S == LBM_F16_OFFSET ? 0 : 64 * 19 * (int)sizeof(typename Store<S>::T);
+  return PH != kPhaseAAGather && (S == LBM_F64 || (S == LBM_F32_OFFSET && !MRT))
+             ? 64 * 19 * (int)sizeof(typename Store<S>::T)
+             : 0;
 }
 
 // The nodes of one 4x4x4 tile: gather, collide, store (into `stage`, where
@@ -308,7 +311,7 @@ __device__ __forceinline__ void step19_nodes(int64_t tile, const NbRec &own, in_
   const uint32_t nw = (uint32_t)__popcll(M);  // the run of one direction in the staged region
   auto put = [&](auto I, R out) {
     constexpr int i = decltype(I)::value;
-    if constexpr (stage_bytes<S, PH>() != 0) {
+    if constexpr (stage_bytes<S, PH, MRT>() != 0) {
       constexpr int slot = PH == kTwoCopy ? i : L::Opp[i];
       St::store(reinterpret_cast<T *>(stage) + (uint32_t)slot * nw, (int64_t)rank, out, a.f16_scale);
       return;
@@ -402,7 +405,7 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src, 
   using T = typename Store<S>::T;
   const NbRec own = nrec[tile];
   step19_nodes<S, NT, INC, PH, MRT, SH>(tile, own, src, dst, a, nrec, nrow, rbase, coef, stage);
-  if constexpr (stage_bytes<S, PH>() != 0) {
+  if constexpr (stage_bytes<S, PH, MRT>() != 0) {
     const uint32_t lane = threadIdx.x & 63, nw = (uint32_t)__popcll(own.mask);
     T *region = static_cast<T *>(dst) + own.off;
     wave_lds_sync();
@@ -444,7 +447,7 @@ __global__ void __launch_bounds__(64 * WPB)
              const int32_t *__restrict__ count) {
   extern __shared__ __attribute__((aligned(16))) char stage_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  char *stage = stage_lds + wv * stage_bytes<S, PH>();
+  char *stage = stage_lds + wv * stage_bytes<S, PH, MRT>();
   // XCD assignment, chosen per form by measurement: chunks of 8 blocks for
   // the two-copy FP64/FP32 step (BGK and MRT), 16 for the FP64 BGK single
   // copy, one contiguous range per XCD for everything else (FP16, the other
@@ -534,7 +537,7 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
     constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
     constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
     auto go = [&](auto kern) {
-      constexpr int lds = W * stage_bytes<S, PH>();
+      constexpr int lds = W * stage_bytes<S, PH, MRT>();
       const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * W), lds, s, src, dst, a, nrec, nrow, rbase, coef, list, count);
@@ -564,7 +567,7 @@ hipError_t step19_persistent_blocks(const Variant &v, bool single_copy, bool shu
     return with_variant(v, phase, shuffle, [&](auto sc, auto wc, auto ic, auto pc, auto mc, auto hc) -> hipError_t {
       constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
       constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
-      constexpr int lds = W * stage_bytes<S, PH>();
+      constexpr int lds = W * stage_bytes<S, PH, MRT>();
       auto kern = k_step19<S, W, true, INC, PH, MRT, kPersistent, SH>;
       int k = 0;
       hipError_t r = allow_lds(reinterpret_cast<const void *>(kern), lds);
