@@ -277,6 +277,9 @@ struct SampleRec {
   int64_t nbase0;   // first fluid node (compact numbering)
   int64_t n_fluid;  // fluid nodes of this sample
   int32_t shape[3]; // nx, ny, nz
+  int32_t tgrid[3]; // tiles per axis
+  int64_t map0;     // first entry of the sample's tile map
+  int64_t group0;   // first group of four x-neighbouring places (kernels.hip)
   int32_t frozen;   // 1: out of the active list (single copy: its state is in layout 0)
 };
 
@@ -318,6 +321,17 @@ struct TileArgs {
   int32_t aa_phase;        // -1: two copies; single copy: layout of the state (0 or 1, see kernels.hip)
   MrtRates mrt;            // relaxation of the MRT collision
   LidArgs lid;             // moving wall on one face of the box
+};
+
+// The tile mesh as the kernels over dense fields go through it (in an argument
+// of its own: the step's launches do not carry it).
+struct MeshArgs {
+  const int32_t *tmap;     // per sample, x fastest: tile of every place of the mesh, -1 where empty
+  const int32_t *groups;   // groups of four x-neighbouring places (one in 2D) that hold a tile
+  int64_t n_listed;        // how many
+  int64_t n_groups;        // groups of all samples' meshes
+  int64_t dense_nodes;     // nodes of all samples' lattices
+  int32_t n_samples;
 };
 
 // The density that multiplies the velocity terms of the equilibrium and the

@@ -8,6 +8,7 @@
 namespace lbm {
 
 struct TileArgs;
+struct MeshArgs;
 struct SampleRec;
 struct CollideCoef;
 struct NbRec;
@@ -49,10 +50,13 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
 hipError_t step19_persistent_blocks(const Variant &v, bool single_copy, bool shuffle, int64_t *blocks);
 hipError_t launch_init(const Variant &v, void *dst, const TileArgs &a, const double *rho, const double *u,
                        hipStream_t s);
-hipError_t launch_moments(const Variant &v, const void *src, const TileArgs &a, double *rho, double *u,
-                          hipStream_t s);
-hipError_t launch_export(const Variant &v, const void *src, const TileArgs &a, double *dense, hipStream_t s);
-hipError_t launch_import(const Variant &v, void *dst, const TileArgs &a, const double *dense, hipStream_t s);
+// every node of the dense fields is written, solid ones with 0
+hipError_t launch_moments(const Variant &v, const void *src, const TileArgs &a, const MeshArgs &m, double *rho,
+                          double *u, hipStream_t s);
+hipError_t launch_export(const Variant &v, const void *src, const TileArgs &a, const MeshArgs &m, double *dense,
+                         hipStream_t s);
+hipError_t launch_import(const Variant &v, void *dst, const TileArgs &a, const MeshArgs &m, const double *dense,
+                         hipStream_t s);
 // Moving wall: add the wall's term to the bounce-back entries that the lid
 // nodes of the listed tiles pull next step (slot opp(i) of the two-copy
 // source when own_slot == 0, slot i of the single copy when 1).
@@ -69,6 +73,5 @@ hipError_t launch_residual_partial(const Variant &v, const void *src, const Tile
 int reduce_chunks();
 hipError_t launch_reduce_final(const double *part, int ncomp, const SampleRec *samples, int n_samples,
                                int words, double *chunk, double *out, hipStream_t s);
-hipError_t launch_fill(double *p, int64_t n, double v, hipStream_t s);
 
 }  // namespace lbm

@@ -24,14 +24,16 @@ size_t align_up(size_t v, size_t a) { return (v + a - 1) / a * a; }
 
 // Byte offsets of every workspace array, plus the host tables to upload.
 struct Plan {
-  size_t buf[2], rec, fluid, pre, nbr, coord, nbase, samples, coef, nrec, nrow, rbase, list, lid, count, part, chunk, out,
+  size_t buf[2], rec, fluid, pre, nbr, coord, nbase, tmap, groups, samples, coef, nrec, nrow, rbase, list, lid, count, part, chunk, out,
       uref, total;
+  int64_t n_groups = 0;  // of places (device.h)
   int64_t entries = 0;  // PDF entries per copy (with region alignment padding)
   // device tables in the solver's internal tile order
   std::vector<lbm::TileRec> rec_h;
   std::vector<uint64_t> fluid_h;
   std::vector<int32_t> pre_h, nbr_h, coord_h;
   std::vector<int64_t> nbase_h;
+  std::vector<int32_t> tmap_h, groups_h;
   std::vector<lbm::SampleRec> samples_h;
   std::vector<lbm::CollideCoef> coef_h;
   // scalar-mask D3Q19 kernel: compact records (+ all-solid sentinel) and rows
@@ -188,6 +190,9 @@ int make_plan(const lbm_tiles *t, const lbm_params *p, const lbm::Variant &v, Pl
       nb += n;
     }
     P.entries = off;
+    P.tmap_h.resize(t->tile_map.size());
+    for (size_t k = 0; k < t->tile_map.size(); ++k)
+      P.tmap_h[k] = t->tile_map[k] < 0 ? -1 : (int32_t)inv[(size_t)t->tile_map[k]];
     // Records of the scalar-mask D3Q19 kernel, one per wavefront: a 4x4x4
     // tile, or one 4x4x4 half (z < 4, z >= 4) of a 4x4x8 tile.  A half's
     // record holds its own fluid mask and its first entry (the tile's offset,
@@ -261,6 +266,20 @@ int make_plan(const lbm_tiles *t, const lbm_params *p, const lbm::Variant &v, Pl
     }
     P.samples_h.resize(t->samples.size());
     P.coef_h.resize(t->samples.size());
+    const int per_group = v.ax == 4 ? 4 : 1;  // places of a workgroup that writes dense fields
+    int64_t groups = 0;
+    auto list_groups = [&](const lbm::Sample &S) {
+      const int gx = (S.tgrid[0] + per_group - 1) / per_group;
+      const int64_t rows = (int64_t)S.tgrid[1] * S.tgrid[2];
+      for (int64_t r = 0; r < rows; ++r)
+        for (int k = 0; k < gx; ++k) {
+          bool any = false;
+          for (int x = k * per_group; x < std::min((k + 1) * per_group, S.tgrid[0]); ++x)
+            any = any || P.tmap_h[(size_t)(S.map0 + x + r * S.tgrid[0])] >= 0;
+          if (any) P.groups_h.push_back((int32_t)(groups + k + r * gx));
+        }
+      return gx * rows;
+    };
     for (size_t s = 0; s < t->samples.size(); ++s) {
       const lbm::Sample &S = t->samples[s];
       lbm::SampleRec &R = P.samples_h[s];
@@ -268,7 +287,11 @@ int make_plan(const lbm_tiles *t, const lbm_params *p, const lbm::Variant &v, Pl
       for (int a = 0; a < 3; ++a) {
         R.g[a] = p->g[a];
         R.shape[a] = S.shape[a];
+        R.tgrid[a] = S.tgrid[a];
       }
+      R.map0 = S.map0;
+      R.group0 = groups;
+      groups += list_groups(S);
       R.dense0 = S.dense0;
       R.n_nodes = S.n_nodes;
       R.tile0 = S.tile0;
@@ -277,6 +300,7 @@ int make_plan(const lbm_tiles *t, const lbm_params *p, const lbm::Variant &v, Pl
       R.n_fluid = S.n_fluid;
       fill_coef(P.coef_h[s], p->g, omega);
     }
+    P.n_groups = groups;
   } catch (const std::bad_alloc &) {
     return set_error(LBM_ERR_NOMEM, "out of host memory planning the workspace");
   }
@@ -295,6 +319,8 @@ int make_plan(const lbm_tiles *t, const lbm_params *p, const lbm::Variant &v, Pl
   P.nbr = take((size_t)(nft * 27) * sizeof(int32_t));
   P.coord = take((size_t)(nft * 3) * sizeof(int32_t));
   P.nbase = take((size_t)nft * sizeof(int64_t));
+  P.tmap = take(P.tmap_h.size() * sizeof(int32_t));
+  P.groups = take(P.groups_h.size() * sizeof(int32_t));
   P.samples = take(t->samples.size() * sizeof(lbm::SampleRec));
   P.coef = take(t->samples.size() * sizeof(lbm::CollideCoef));
   P.nrec = take(P.nrec_h.size() * sizeof(lbm::NbRec));
@@ -318,6 +344,7 @@ struct lbm_solver {
   lbm_params p{};
   hipStream_t stream = nullptr;
   lbm::TileArgs args{};
+  lbm::MeshArgs mesh{};
   void *buf[2] = {nullptr, nullptr};  // the same buffer twice for the single copy
   bool single_copy = false;
   int cur = 0;  // two copies: the copy holding the state; single copy: its layout (0 or 1)
@@ -326,7 +353,6 @@ struct lbm_solver {
   int n_samples = 0;
   int words = 0;
   double omega = 0.0;
-  int64_t dense_nodes = 0;
   std::vector<lbm::SampleRec> samples_h;
   lbm::SampleRec *samples_d = nullptr;
   std::vector<uint32_t> periodic;  // per sample
@@ -421,7 +447,6 @@ extern "C" int lbm_create(const lbm_tiles *t, const lbm_params *p, void *ws, siz
   s->n_samples = (int)t->samples.size();
   s->words = t->words;
   s->omega = std::isinf(p->tau) ? 0.0 : 1.0 / p->tau;
-  s->dense_nodes = t->n_nodes;
   s->samples_h = P.samples_h;
   s->samples_d = reinterpret_cast<lbm::SampleRec *>(base + P.samples);
   s->coef_h = P.coef_h;
@@ -488,6 +513,12 @@ extern "C" int lbm_create(const lbm_tiles *t, const lbm_params *p, void *ws, siz
   a.nbr = reinterpret_cast<const int32_t *>(base + P.nbr);
   a.coord = reinterpret_cast<const int32_t *>(base + P.coord);
   a.nbase = reinterpret_cast<const int64_t *>(base + P.nbase);
+  s->mesh.tmap = reinterpret_cast<const int32_t *>(base + P.tmap);
+  s->mesh.groups = reinterpret_cast<const int32_t *>(base + P.groups);
+  s->mesh.n_listed = (int64_t)P.groups_h.size();
+  s->mesh.n_groups = P.n_groups;
+  s->mesh.dense_nodes = t->n_nodes;
+  s->mesh.n_samples = s->n_samples;
   a.samples = s->samples_d;
   a.n_waves = t->n_ftiles * t->words;
   a.n_fluid = t->n_fluid;
@@ -520,6 +551,8 @@ extern "C" int lbm_create(const lbm_tiles *t, const lbm_params *p, void *ws, siz
   if (e == hipSuccess && s->scalar_mask && p->persistent)
     e = lbm::step19_persistent_blocks(v, s->single_copy, s->shuffle, &s->persistent_blocks);
   if (e == hipSuccess) e = up(P.nbase, P.nbase_h.data(), (size_t)nft * sizeof(int64_t));
+  if (e == hipSuccess) e = up(P.tmap, P.tmap_h.data(), P.tmap_h.size() * sizeof(int32_t));
+  if (e == hipSuccess) e = up(P.groups, P.groups_h.data(), P.groups_h.size() * sizeof(int32_t));
   if (e == hipSuccess) e = up(P.samples, P.samples_h.data(), P.samples_h.size() * sizeof(lbm::SampleRec));
   if (e == hipSuccess) e = hipStreamSynchronize(s->stream);  // host tables may be freed after return
   if (e != hipSuccess) {
@@ -761,9 +794,7 @@ extern "C" int64_t lbm_step_count(const lbm_solver *s) { return s ? s->steps : -
 extern "C" int lbm_moments(lbm_solver *s, double *rho, double *u) {
   if (!s) return set_error(LBM_ERR_ARG, "lbm_moments: NULL solver");
   if (!s->initialized) return set_error(LBM_ERR_STATE, "lbm_moments: solver not initialised");
-  if (rho) HIP_TRY(lbm::launch_fill(rho, s->dense_nodes, 0.0, s->stream));
-  if (u) HIP_TRY(lbm::launch_fill(u, 3 * s->dense_nodes, 0.0, s->stream));
-  HIP_TRY(lbm::launch_moments(s->var, s->buf[s->cur], aux_args(s), rho, u, s->stream));
+  HIP_TRY(lbm::launch_moments(s->var, s->buf[s->cur], aux_args(s), s->mesh, rho, u, s->stream));
   return LBM_OK;
 }
 
@@ -812,15 +843,14 @@ extern "C" int lbm_residual(lbm_solver *s, double *out_host) {
 extern "C" int lbm_pdfs_export(lbm_solver *s, double *dev_dense) {
   if (!s || !dev_dense) return set_error(LBM_ERR_ARG, "lbm_pdfs_export: NULL argument");
   if (!s->initialized) return set_error(LBM_ERR_STATE, "lbm_pdfs_export: solver not initialised");
-  HIP_TRY(lbm::launch_fill(dev_dense, (int64_t)s->var.q * s->dense_nodes, 0.0, s->stream));
-  HIP_TRY(lbm::launch_export(s->var, s->buf[s->cur], aux_args(s), dev_dense, s->stream));
+  HIP_TRY(lbm::launch_export(s->var, s->buf[s->cur], aux_args(s), s->mesh, dev_dense, s->stream));
   return LBM_OK;
 }
 
 extern "C" int lbm_pdfs_import(lbm_solver *s, const double *dev_dense) {
   if (!s || !dev_dense) return set_error(LBM_ERR_ARG, "lbm_pdfs_import: NULL argument");
   if (s->single_copy) s->cur = 0;  // import writes layout 0
-  HIP_TRY(lbm::launch_import(s->var, s->buf[s->cur], aux_args(s), dev_dense, s->stream));
+  HIP_TRY(lbm::launch_import(s->var, s->buf[s->cur], aux_args(s), s->mesh, dev_dense, s->stream));
   s->initialized = true;
   return LBM_OK;
 }
