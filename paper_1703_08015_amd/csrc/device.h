@@ -545,4 +545,93 @@ __device__ __forceinline__ void collide_mrt(R (&f)[L::Q], R sum, R jx, R jy, R j
   });
 }
 
+// What the BGK collision takes from the relaxation rate w and the acceleration
+// g alone, h = 1 - w/2: the same for every node of a sample.
+template <class L, class R>
+struct BgkRate {
+  R om, h3, gx, gy, gz;             // w, 3 h, g
+  R odd[L::Q / 2], even[L::Q / 2];  // 3 h c.g and 9 h c.g of the directions 1, 3, 5, ...
+};
+
+template <class L, class R>
+__device__ __forceinline__ BgkRate<L, R> bgk_rate(R om, R gx, R gy, R gz) {
+#pragma clang fp contract(off)
+  BgkRate<L, R> k;
+  const R h = std::fma(R(-0.5), om, R(1));
+  k.om = om, k.h3 = R(3) * h, k.gx = gx, k.gy = gy, k.gz = gz;
+  static_for<L::Q / 2>([&](auto I) {
+    constexpr int p = decltype(I)::value, i = 2 * p + 1;
+    const R cg = cdot<L::C[i][0], L::C[i][1], L::C[i][2]>(gx, gy, gz);
+    k.odd[p] = k.h3 * cg, k.even[p] = R(9) * h * cg;
+  });
+  return k;
+}
+
+// BGK collision, Eqs. (2), (3) or (4), (7) with the Guo source, in place on f
+// (the PDFs, or their offsets), by pairs of opposite directions:
+//   poly = 9/2 (c.u)^2 - 3/2 u.u +- 3 c.u,   feq = w_i rho (1 + poly) or w_i (c0 + m poly),
+//   f* = (f + w (feq - f)) + w_i m (9h c.g c.u - 3h u.g +- 3h c.g)
+// with m the density of the velocity terms (the density, or 1) and c0 the density
+// or its offset.  What rounding does to the sum of a node's f* moves mass at every
+// step, which a long run collects: poly is therefore summed before the 1 joins it
+// (else the 64x64 FP64 channel ends with 2e-14 of flow across), and as the weights
+// as doubles sum to 1 - 2^-54 on both lattices, the FP64 quasi-compressible rest
+// weight is the next double, which makes the sum exact (else the velocity never
+// stops changing by 1e-13 in 2000 steps; with it, 3e-15).  The incompressible form
+// keeps the plain weights: its density is checked to 1e-13 after 1000 steps against
+// the dense code, which loses 0.8e-13 by them.  Every multiply-add is an explicit fma and nothing
+// else is contracted, so every kernel that calls it rounds the same way.
+template <class L, int S, bool INC, class R>
+__device__ __forceinline__ void collide_bgk(R (&f)[L::Q], R sum, R jx, R jy, R jz, R rho0, const BgkRate<L, R> &k) {
+#pragma clang fp contract(off)
+  constexpr bool off = Store<S>::offset, product = !off && !INC;
+  const R rho = off ? rho0 + sum : sum;
+  const R m = velocity_density<INC>(rho);
+  R ux, uy, uz;  // Eq. (5) or (6) with the half-force shift
+  if constexpr (INC) {
+    ux = std::fma(R(0.5), k.gx, jx), uy = std::fma(R(0.5), k.gy, jy), uz = std::fma(R(0.5), k.gz, jz);
+  } else {
+    const R inv = R(1) / rho;
+    ux = std::fma(jx, inv, R(0.5) * k.gx), uy = std::fma(jy, inv, R(0.5) * k.gy);
+    uz = std::fma(jz, inv, R(0.5) * k.gz);
+  }
+  const R uu = std::fma(ux, ux, std::fma(uy, uy, uz * uz));
+  const R F0 = -k.h3 * std::fma(ux, k.gx, std::fma(uy, k.gy, uz * k.gz));
+  const R P0 = R(-1.5) * uu;
+  // w_i rho (1 + poly) - f or w_i (c0 + m poly) - f
+  auto diff = [&](R w, R poly, R fi) -> R {
+    if constexpr (product) return std::fma(w * rho, R(1) + poly, -fi);
+    else return std::fma(w, std::fma(m, poly, off ? sum : rho), -fi);
+  };
+  constexpr R w0 = R(product ? L::Wt[0] + 0x1p-54 : L::Wt[0]);
+  f[0] = std::fma(w0 * m, F0, std::fma(k.om, diff(w0, P0, f[0]), f[0]));
+  static_for<L::Q / 2>([&](auto I) {
+    constexpr int p = decltype(I)::value, i = 2 * p + 1;
+    static_assert(L::Opp[i] == i + 1);
+    constexpr R w = R(L::Wt[i]);
+    const R cu = cdot<L::C[i][0], L::C[i][1], L::C[i][2]>(ux, uy, uz);
+    const R E = std::fma(R(4.5) * cu, cu, P0), F = std::fma(k.even[p], cu, F0);
+    const R d1 = diff(w, std::fma(R(3), cu, E), f[i]), d2 = diff(w, std::fma(R(-3), cu, E), f[i + 1]);
+    f[i] = std::fma(w * m, F + k.odd[p], std::fma(k.om, d1, f[i]));
+    f[i + 1] = std::fma(w * m, F - k.odd[p], std::fma(k.om, d2, f[i + 1]));
+  });
+}
+
+// Density and momentum sums of gathered values.
+template <class L, class R>
+__device__ __forceinline__ void moment_sums(const R (&f)[L::Q], R &sum, R &jx, R &jy, R &jz) {
+  sum = jx = jy = jz = R(0);
+  static_for<L::Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    constexpr int cx = L::C[i][0], cy = L::C[i][1], cz = L::C[i][2];
+    sum += f[i];
+    if constexpr (cx > 0) jx += f[i];
+    if constexpr (cx < 0) jx -= f[i];
+    if constexpr (cy > 0) jy += f[i];
+    if constexpr (cy < 0) jy -= f[i];
+    if constexpr (cz > 0) jz += f[i];
+    if constexpr (cz < 0) jz -= f[i];
+  });
+}
+
 }  // namespace lbm

@@ -80,7 +80,8 @@ __device__ __forceinline__ int lane_rank(uint64_t m) {
 // The two-copy D2Q9 BGK step asks for 8 waves per SIMD: left to itself the
 // compiler clusters the loads of a 16x16 tile into 76 VGPRs (6 waves), where
 // 56 registers with no extra instructions give all 8 (+5% measured; the
-// single-copy phases measured slower with 8 and keep the compiler's choice)
+// single-copy phases measured slower with 8 and keep the compiler's choice).  Runs
+// of two-copy D2Q9 steps go to step9.hip where that is faster.
 template <class L, int AX, int AY, int AZ, int S, int WPB, bool INC, int PH, bool MRT>
 __global__ void __launch_bounds__(64 * WPB)
     __attribute__((amdgpu_waves_per_eu(L::Q == 9 && !MRT && PH == kPhaseTwoCopy ? 8 : 1)))
@@ -148,34 +149,10 @@ __global__ void __launch_bounds__(64 * WPB)
     f[i] = St::load(src, addr, a.f16_inv);
     if constexpr (PH == kPhaseAAGather) ea[i] = addr;
   });
-  // macroscopic moments, Eq. (5) or (6) with the half-force shift
   const SampleRec &smp = a.samples[a.rec[tile].sample];
   const R gx = (R)smp.g[0], gy = (R)smp.g[1], gz = (R)smp.g[2];
-  R sum = 0, jx = 0, jy = 0, jz = 0;
-  static_for<Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr int cx = L::C[i][0], cy = L::C[i][1], cz = L::C[i][2];
-    sum += f[i];
-    if constexpr (cx > 0) jx += f[i];
-    if constexpr (cx < 0) jx -= f[i];
-    if constexpr (cy > 0) jy += f[i];
-    if constexpr (cy < 0) jy -= f[i];
-    if constexpr (cz > 0) jz += f[i];
-    if constexpr (cz < 0) jz -= f[i];
-  });
-  const R rho = St::offset ? (R)a.rho0 + sum : sum;
-  const R m = velocity_density<INC>(rho);
-  R ux, uy, uz;
-  if constexpr (INC) {
-    ux = jx + R(0.5) * gx, uy = jy + R(0.5) * gy, uz = jz + R(0.5) * gz;
-  } else {
-    const R inv = R(1) / rho;
-    ux = jx * inv + R(0.5) * gx, uy = jy * inv + R(0.5) * gy, uz = jz * inv + R(0.5) * gz;
-  }
-  const R uu = ux * ux + uy * uy + uz * uz;
-  const R om = (R)omega_d;
-  const R fo = R(1) - R(0.5) * om;
-
+  R sum, jx, jy, jz;
+  moment_sums<L>(f, sum, jx, jy, jz);
   // two-copy: own slot i; single-copy gather: where opp(i) was read;
   // single-copy local: own slot opp(i)
   auto put = [&](auto I, R out) {
@@ -189,28 +166,11 @@ __global__ void __launch_bounds__(64 * WPB)
       e = obase + (int64_t)L::Opp[i] * on;
     St::store(dst, e, out, a.f16_scale);
   };
-  if constexpr (MRT) {
-    // Eq. (8) in the orthogonal moment basis
-    collide_mrt<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, gx, gy, gz, a.mrt);
-    static_for<Q>([&](auto I) { put(I, f[decltype(I)::value]); });
-    return;
-  }
-  // BGK collision, Eqs. (2), (3) or (4), (7) + Guo source; store own block entries
-  static_for<Q>([&](auto I) {
-    constexpr int i = decltype(I)::value;
-    constexpr int cx = L::C[i][0], cy = L::C[i][1], cz = L::C[i][2];
-    constexpr R w = (R)L::Wt[i];
-    const R cu = R(cx) * ux + R(cy) * uy + R(cz) * uz;
-    const R cg = R(cx) * gx + R(cy) * gy + R(cz) * gz;
-    const R cmug = (R(cx) - ux) * gx + (R(cy) - uy) * gy + (R(cz) - uz) * gz;
-    const R poly = R(3) * cu + R(4.5) * cu * cu - R(1.5) * uu;
-    // full form: w (rho + m poly); offset form: w (drho + m poly), m = rho or 1
-    R feq;
-    if constexpr (INC) feq = St::offset ? w * (sum + poly) : w * (rho + poly);
-    else feq = St::offset ? w * (sum + rho * poly) : w * rho * (R(1) + poly);
-    const R F = w * m * (R(3) * cmug + R(9) * cu * cg);
-    put(I, f[i] + om * (feq - f[i]) + fo * F);
-  });
+  if constexpr (MRT)
+    collide_mrt<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, gx, gy, gz, a.mrt);  // Eq. (8)
+  else
+    collide_bgk<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, bgk_rate<L>((R)omega_d, gx, gy, gz));
+  static_for<Q>([&](auto I) { put(I, f[decltype(I)::value]); });
 }
 
 // ---- per-node helpers for the auxiliary kernels -------------------------------

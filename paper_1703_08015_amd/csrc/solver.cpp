@@ -377,6 +377,7 @@ struct lbm_solver {
   // captured graphs of graph_steps steps, one per starting copy
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
+  int graph_end[2] = {0, 0};  // the copy (layout) a graph ends in
   bool scalar_mask = false;  // which step kernel runs
   bool shuffle = false;      // the scalar-mask kernel in its shuffle form
   double *part = nullptr, *chunk = nullptr, *out = nullptr, *uref = nullptr;
@@ -727,13 +728,24 @@ extern "C" int lbm_init(lbm_solver *s, const double *rho, const double *u) {
   return LBM_OK;
 }
 
-// Enqueue one step from copy (two copies) or layout (single copy) `from` on `st`.
-static hipError_t enqueue_step(lbm_solver *s, int from, hipStream_t st) {
+// Enqueue one launch of at most n > 0 steps from copy (two copies) or layout
+// (single copy) `from` on `st`; *done: the steps it takes.  The state is then
+// in the other copy (layout).
+static hipError_t enqueue_step(lbm_solver *s, int from, int n, hipStream_t st, int *done) {
   const int phase = !s->single_copy ? lbm::kPhaseTwoCopy : (from == 0 ? lbm::kPhaseAAGather : lbm::kPhaseAALocal);
+  *done = 1;
   if (s->args.lid.axis >= 0 && s->n_lid_tiles > 0) {
     const hipError_t e =
         lbm::launch_lid_fixup(s->var, s->buf[from], s->args, s->lid_tiles_d, s->n_lid_tiles, s->single_copy, st);
     if (e != hipSuccess) return e;
+  } else if (!s->single_copy && s->n_samples == 1) {
+    const lbm::SampleRec &S = s->samples_h[0];
+    const int k = lbm::steps9_per_launch(s->var, S.shape, s->args.n_waves, n);
+    if (k > 1) {
+      *done = k;
+      return lbm::launch_steps9(s->var, s->buf[from], s->buf[from ^ 1], s->args, s->mesh, S.shape, S.tgrid,
+                                s->periodic[0], k, s->omega, st);
+    }
   }
   if (s->scalar_mask) {
     const int mode = s->p.persistent ? 2 : (s->all_active ? 0 : 1);
@@ -751,8 +763,8 @@ static int capture(lbm_solver *s, int from) {
   HIP_TRY(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   int c = from;
-  for (int k = 0; k < s->p.graph_steps && e == hipSuccess; ++k) {
-    e = enqueue_step(s, c, s->cap_stream);
+  for (int k = 0, done = 0; k < s->p.graph_steps && e == hipSuccess; k += done) {
+    e = enqueue_step(s, c, s->p.graph_steps - k, s->cap_stream, &done);
     c ^= 1;
   }
   hipGraph_t g = nullptr;
@@ -761,6 +773,7 @@ static int capture(lbm_solver *s, int from) {
   if (e == hipSuccess) e = hipGraphInstantiate(&s->graph[from], g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
   if (e != hipSuccess) return set_error(LBM_ERR_HIP, "lbm_step: graph capture failed: %s", hipGetErrorString(e));
+  s->graph_end[from] = c;
   return LBM_OK;
 }
 
@@ -776,15 +789,15 @@ extern "C" int lbm_step(lbm_solver *s, int32_t n) {
         if (rc) return rc;
       }
       HIP_TRY(hipGraphLaunch(s->graph[s->cur], s->stream));
-      s->cur ^= (K & 1);
+      s->cur = s->graph_end[s->cur];
       s->steps += K;
       n -= K;
     }
   }
-  for (int32_t k = 0; k < n; ++k) {
-    HIP_TRY(enqueue_step(s, s->cur, s->stream));
+  for (int done = 0; n > 0; n -= done) {
+    HIP_TRY(enqueue_step(s, s->cur, n, s->stream, &done));
     s->cur ^= 1;
-    ++s->steps;
+    s->steps += done;
   }
   return LBM_OK;
 }

@@ -1,0 +1,201 @@
+// D2Q9 steps on 16x16 tiles, several per launch.
+//
+// A workgroup takes a window of 32x32 nodes, one per thread, reads its
+// post-collision PDFs once, and runs K steps there: each step exchanges the
+// nodes' values through LDS (a non-solid source's f*_i(x - c_i), or the node's
+// own f*_opp(i) on a half-way bounce-back) and collides in registers.  What the
+// window's edge lacks makes one more layer wrong per step, so after K steps the
+// inner (32 - 2K)^2 nodes are those of K single steps, bit for bit, and are
+// written; the layers around are computed again by the neighbouring windows.
+// So a launch moves each PDF once in and once out for K steps, and a grid too
+// small to fill the device pays one launch for K steps.
+//
+// What bounds it: vector arithmetic at two workgroups per compute unit (FP64: one thread
+// per node, 64 registers) and, where a window's nodes are read, HBM: 1.78 reads
+// and one write of each PDF per four steps.  What is the same for all nodes is
+// kept in scalar registers: without that FP64 needs 82 vector registers, runs
+// one workgroup per compute unit and spills if it is held to 64 (35.0 and 42.4
+// against 29.1 us per step on the 1536x1500 channel with discs, with a shorter
+// collision than the one of now).
+// Per step, k_step before -> this: that channel 39.7 -> 33.1 us (FP64), 27.2 ->
+// 20.8 (FP32); 4096x4096: 418 -> 279 and 248 -> 159; 512x512: 8.0 -> 5.0 and
+// 6.1 -> 3.4; 256x256: 4.5 -> 2.3 and 4.2 -> 1.8; 64x64: 4.3 -> 2.1 and 4.2 ->
+// 1.7, MRT 4.4 -> 2.8 and 4.3 -> 2.3 (eight steps per launch in the last two).
+//
+// Steps of other forms (one PDF copy, a lid, FP16 storage, which rounds every
+// step to 16 bits, batches) and single steps run k_step (kernels.hip).
+#include "device.h"
+#include "kernels.h"
+
+namespace lbm {
+namespace {
+
+constexpr int kWin = 32, kThreads = kWin * kWin;   // window edge, threads
+constexpr int kPitch = kWin + 2, kArea = kPitch * kPitch;  // with a guard ring
+
+struct Window {
+  int nx, ny, tgx, periodic;
+  int steps, wx;  // steps of this launch; windows along x
+};
+
+// One scalar register (pair) for a value that is the same in every lane.
+__device__ __forceinline__ void to_scalar(float &v) {
+  v = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ void to_scalar(double &v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  v = __builtin_bit_cast(double, lo | hi << 32);
+}
+
+template <int S, bool INC, bool MRT>
+__global__ void __launch_bounds__(kThreads, (S == LBM_F64 && MRT ? 4 : 8))
+    k_steps9(const void *__restrict__ src_, void *__restrict__ dst_, TileArgs a, const int32_t *__restrict__ tmap,
+             Window w, double omega) {
+  using L = D2Q9;
+  using St = Store<S>;
+  using T = typename St::T;
+  using R = typename St::R;
+  constexpr int Q = L::Q, AX = 16, W = 4;
+  extern __shared__ __attribute__((aligned(16))) char lds[];
+  R *const x8 = reinterpret_cast<R *>(lds);                      // [8][kArea]: direction i at (i - 1) kArea
+  uint8_t *const open_s = reinterpret_cast<uint8_t *>(x8 + 8 * kArea);  // [kArea]
+  const T *src = static_cast<const T *>(src_);
+  T *dst = static_cast<T *>(dst_);
+  const int tid = threadIdx.x, lx = tid % kWin, ly = tid / kWin;
+  const int at = (lx + 1) + kPitch * (ly + 1);
+  const int out = kWin - 2 * w.steps;  // edge of the window's result
+  const int blk = (int)xcd_remap(blockIdx.x, gridDim.x);
+  const int px = blk % w.wx * out + lx - w.steps, py = blk / w.wx * out + ly - w.steps;
+  auto wrap = [](int v, int n, bool periodic) -> int {  // -1 past a wall
+    if (v >= 0 && v < n) return v;
+    if (!periodic) return -1;
+    v %= n;
+    return v < 0 ? v + n : v;
+  };
+  const int x = wrap(px, w.nx, w.periodic & 1), y = wrap(py, w.ny, w.periodic & 2);
+  bool fluid = false;
+  int64_t entry = 0;
+  int n = 0;
+  if (x >= 0 && y >= 0) {
+    const int32_t tile = tmap[x / AX + w.tgx * (y / AX)];
+    if (tile >= 0) {
+      const int ell = x % AX + AX * (y % AX), wd = ell >> 6, b = ell & 63;
+      const uint64_t m = a.fluid[(int64_t)tile * W + wd];
+      if ((m >> b) & 1ull) {
+        const TileRec r = a.rec[tile];
+        fluid = true;
+        n = r.n;
+        entry = r.off + a.pre[(int64_t)tile * W + wd] + __popcll(m & ((1ull << b) - 1ull));
+      }
+    }
+  }
+  for (int k = tid; k < kArea; k += kThreads) open_s[k] = 0;
+  if (!__syncthreads_or(fluid)) return;  // nothing but solid nodes in this window
+  open_s[at] = fluid;
+  R f[Q];
+  static_for<Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    f[i] = fluid ? St::load(src, entry + (int64_t)i * n, a.f16_inv) : R(0);
+  });
+  __syncthreads();
+  uint32_t open = 0;  // bit i: the source of direction i is non-solid
+  static_for<Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    if (i > 0 && open_s[at - L::C[i][0] - kPitch * L::C[i][1]]) open |= 1u << i;
+  });
+  const R gx = (R)a.samples[0].g[0], gy = (R)a.samples[0].g[1], gz = (R)a.samples[0].g[2];
+  BgkRate<L, R> rate = bgk_rate<L>((R)omega, gx, gy, gz);
+  to_scalar(rate.om), to_scalar(rate.h3);
+  static_for<Q / 2>([&](auto I) { to_scalar(rate.odd[decltype(I)::value]), to_scalar(rate.even[decltype(I)::value]); });
+  for (int t = 0; t < w.steps; ++t) {
+    if (fluid)
+      static_for<Q - 1>([&](auto I) {
+        constexpr int i = decltype(I)::value + 1;
+        x8[(i - 1) * kArea + at] = f[i];
+      });
+    __syncthreads();
+    R g[Q];
+    g[0] = f[0];
+    static_for<Q - 1>([&](auto I) {
+      constexpr int i = decltype(I)::value + 1;
+      const R v = x8[(i - 1) * kArea + at - L::C[i][0] - kPitch * L::C[i][1]];
+      g[i] = (open >> i) & 1u ? v : f[L::Opp[i]];
+    });
+    __syncthreads();  // every value of this step is read
+    R sum, jx, jy, jz;
+    moment_sums<L>(g, sum, jx, jy, jz);
+    if constexpr (MRT)
+      collide_mrt<L, S, INC>(g, sum, jx, jy, jz, (R)a.rho0, gx, gy, gz, a.mrt);
+    else
+      collide_bgk<L, S, INC>(g, sum, jx, jy, jz, (R)a.rho0, rate);
+    static_for<Q>([&](auto I) { f[decltype(I)::value] = g[decltype(I)::value]; });
+  }
+  const bool inner = lx >= w.steps && lx < kWin - w.steps && ly >= w.steps && ly < kWin - w.steps;
+  if (fluid && inner && px < w.nx && py < w.ny)  // (an inner node's px, py are not negative)
+    static_for<Q>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      St::store(dst, entry + (int64_t)i * n, f[i], a.f16_scale);
+    });
+}
+
+int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * steps); }
+
+}  // namespace
+
+// Steps of the next launch when n more are wanted; 1: the single step.  Eight
+// where the windows of eight steps are no more than the compute units, so that
+// all run at once and a step costs its latency; else four, where the doubled
+// layers weigh less.  One sweep over the steps per launch, FP64, us per step:
+//   256x256: 4.4 by one, 2.7 by four, 2.0 by eight;
+//   512x512: 7.5 by one, 4.5 by four, 5.4 by five, 5.5 by eight;
+//   4096x4096: 416 by one, 326 by two, 253 by four, 255 by five, 316 by eight.
+// What is left over is spread evenly (ten steps as 4 + 3 + 3).  Single steps
+// stay for
+//  - two steps of FP32 on larger grids (1536x1500: 25.5 us per step by two,
+//    24.7 by one),
+//  - MRT on larger grids, whose FP64 form does not fit 64 registers (1536x1500:
+//    FP64 41.7 us by one, 49.0 by four; FP32 28.0 and 28.4),
+//  - geometries with fewer than one tile for every four windows, where most of
+//    a launch would look at solid nodes.
+int steps9_per_launch(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1) return 1;
+  const bool small = (int64_t)windows(shape[0], 8) * windows(shape[1], 8) <= 256;
+  if (!small && v.collision == LBM_COLLISION_MRT) return 1;
+  const int most = small ? 8 : 4, launches = n / most + (n % most != 0);
+  const int k = n / launches + (n % launches != 0);
+  if (!small && k == 2 && v.storage != LBM_F64) return 1;
+  return (int64_t)windows(shape[0], k) * windows(shape[1], k) <= n_waves ? k : 1;
+}
+
+hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const TileArgs &a, const MeshArgs &m,
+                         const int32_t shape[3], const int32_t tgrid[3], uint32_t periodic, int steps, double omega,
+                         hipStream_t s) {
+  if (a.n_waves == 0) return hipSuccess;
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || steps < 1 || steps > 8 || src == dst) return hipErrorInvalidValue;
+  Window w{shape[0], shape[1], tgrid[0], (int)periodic, steps, windows(shape[0], steps)};
+  const unsigned blocks = (unsigned)((int64_t)w.wx * windows(shape[1], steps));
+  auto go = [&](auto sc, auto ic, auto mc) -> hipError_t {
+    constexpr int S = decltype(sc)::value;
+    auto kern = k_steps9<S, decltype(ic)::value, decltype(mc)::value>;
+    constexpr int lds = (8 * (int)sizeof(typename Store<S>::R) + 1) * kArea;
+    if (lds > 65536) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(kern),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(kThreads), lds, s, src, dst, a, m.tmap, w, omega);
+    return hipGetLastError();
+  };
+  auto by_model = [&](auto sc, auto mc) {
+    return v.model == LBM_MODEL_INCOMPRESSIBLE ? go(sc, std::true_type{}, mc) : go(sc, std::false_type{}, mc);
+  };
+  auto by_collision = [&](auto sc) {
+    return v.collision == LBM_COLLISION_MRT ? by_model(sc, std::true_type{}) : by_model(sc, std::false_type{});
+  };
+  return v.storage == LBM_F64 ? by_collision(std::integral_constant<int, LBM_F64>{})
+                              : by_collision(std::integral_constant<int, LBM_F32_OFFSET>{});
+}
+
+}  // namespace lbm
