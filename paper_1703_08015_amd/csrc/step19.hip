@@ -158,18 +158,26 @@ constexpr int kTwoCopy = kPhaseTwoCopy, kAAGather = kPhaseAAGather, kAALocal = k
 // and whose step is bound by vector issue, gains 3% there and loses 1% on a
 // 256^3 vessel tree, and stores directly, as does FP32 with the MRT collision
 // (2% slower staged) and the gather/scatter step, which writes its neighbours'
-// entries.
-template <int S, int PH, bool MRT>
+// entries.  A launch of so few tiles that all their wavefronts run at once ends
+// with the slowest wavefront, and the way through LDS makes each one longer:
+// it stores directly (few_tiles).  48^3 spheres (up to 1,728 tiles), without / with:
+// FP64 6.6 / 6.8, FP32 6.0 / 6.2; 64^3 (4,096): FP64 11.7 / 11.3, FP32 7.2 /
+// 7.6; 80^3 (8,000): 19.0 / 18.2 and 11.7 / 11.5.
+template <int S, int PH, bool MRT, bool STAGE = true>
 constexpr int stage_bytes() {
-  return PH != kPhaseAAGather && (S == LBM_F64 || (S == LBM_F32_OFFSET && !MRT))
+  return STAGE && PH != kPhaseAAGather && (S == LBM_F64 || (S == LBM_F32_OFFSET && !MRT))
              ? 64 * 19 * (int)sizeof(typename Store<S>::T)
              : 0;
+}
+template <int S>
+bool few_tiles(int64_t waves) {  // two wavefronts per SIMD of FP64, four of FP32
+  return waves <= (S == LBM_F64 ? 2048 : 4096);
 }
 
 // The nodes of one 4x4x4 tile: gather, collide, store (into `stage`, where
 // there is one).  Lanes of solid nodes return early (in the shuffle form SH
 // after the shuffles); every value the wavefront branches on is uniform.
-template <int S, bool NT, bool INC, int PH, bool MRT, bool SH>
+template <int S, bool NT, bool INC, int PH, bool MRT, bool SH, bool STAGE>
 __device__ __forceinline__ void step19_nodes(int64_t tile, const NbRec &own, in_ptr<PH, void> src_,
                                              out_ptr<PH, void> dst_, const TileArgs &a,
                                              const NbRec *__restrict__ nrec, const uint32_t *__restrict__ nrow,
@@ -311,7 +319,7 @@ __device__ __forceinline__ void step19_nodes(int64_t tile, const NbRec &own, in_
   const uint32_t nw = (uint32_t)__popcll(M);  // the run of one direction in the staged region
   auto put = [&](auto I, R out) {
     constexpr int i = decltype(I)::value;
-    if constexpr (stage_bytes<S, PH, MRT>() != 0) {
+    if constexpr (stage_bytes<S, PH, MRT, STAGE>() != 0) {
       constexpr int slot = PH == kTwoCopy ? i : L::Opp[i];
       St::store(reinterpret_cast<T *>(stage) + (uint32_t)slot * nw, (int64_t)rank, out, a.f16_scale);
       return;
@@ -397,15 +405,15 @@ __device__ __forceinline__ void step19_nodes(int64_t tile, const NbRec &own, in_
 }
 
 // One 4x4x4 tile.  stage: the wavefront's stage_bytes of LDS, 16-byte aligned.
-template <int S, bool NT, bool INC, int PH, bool MRT, bool SH>
+template <int S, bool NT, bool INC, int PH, bool MRT, bool SH, bool STAGE>
 __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src, out_ptr<PH, void> dst,
                                             const TileArgs &a, const NbRec *__restrict__ nrec,
                                             const uint32_t *__restrict__ nrow, const uint32_t *__restrict__ rbase,
                                             const CollideCoef *__restrict__ coef, char *stage) {
   using T = typename Store<S>::T;
   const NbRec own = nrec[tile];
-  step19_nodes<S, NT, INC, PH, MRT, SH>(tile, own, src, dst, a, nrec, nrow, rbase, coef, stage);
-  if constexpr (stage_bytes<S, PH, MRT>() != 0) {
+  step19_nodes<S, NT, INC, PH, MRT, SH, STAGE>(tile, own, src, dst, a, nrec, nrow, rbase, coef, stage);
+  if constexpr (stage_bytes<S, PH, MRT, STAGE>() != 0) {
     const uint32_t lane = threadIdx.x & 63, nw = (uint32_t)__popcll(own.mask);
     T *region = static_cast<T *>(dst) + own.off;
     wave_lds_sync();
@@ -432,8 +440,8 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src, 
   }
 }
 
-// Which tiles a launch visits.
-enum { kDirect = 0, kList = 1, kPersistent = 2 };
+// Which tiles a launch visits; kFew: kDirect, stored directly (few_tiles).
+enum { kDirect = 0, kList = 1, kPersistent = 2, kFew = 3 };
 
 // kDirect: wavefront w updates tile w.  kList: wavefront w updates tile
 // list[w] if w < *count.  kPersistent: a fixed grid of G wavefronts strides
@@ -447,7 +455,8 @@ __global__ void __launch_bounds__(64 * WPB)
              const int32_t *__restrict__ count) {
   extern __shared__ __attribute__((aligned(16))) char stage_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  char *stage = stage_lds + wv * stage_bytes<S, PH, MRT>();
+  constexpr bool STAGE = MODE != kFew;
+  char *stage = stage_lds + wv * stage_bytes<S, PH, MRT, STAGE>();
   // XCD assignment, chosen per form by measurement: chunks of 8 blocks for
   // the two-copy FP64/FP32 step (BGK and MRT), 16 for the FP64 BGK single
   // copy, one contiguous range per XCD for everything else (FP16, the other
@@ -457,16 +466,16 @@ __global__ void __launch_bounds__(64 * WPB)
                                              : (S == LBM_F64 && !MRT ? 16 : 0);
   const int64_t blk = kChunk ? xcd_chunk(blockIdx.x, gridDim.x, kChunk) : xcd_remap(blockIdx.x, gridDim.x);
   const int64_t gw = blk * WPB + wv;
-  if constexpr (MODE == kDirect) {
+  if constexpr (MODE == kDirect || MODE == kFew) {
     if (gw >= a.n_waves) return;
-    step19_tile<S, NT, INC, PH, MRT, SH>(gw, src, dst, a, nrec, nrow, rbase, coef, stage);
+    step19_tile<S, NT, INC, PH, MRT, SH, STAGE>(gw, src, dst, a, nrec, nrow, rbase, coef, stage);
   } else if constexpr (MODE == kList) {
     if (gw >= (int64_t)*count) return;
-    step19_tile<S, NT, INC, PH, MRT, SH>(list[gw], src, dst, a, nrec, nrow, rbase, coef, stage);
+    step19_tile<S, NT, INC, PH, MRT, SH, STAGE>(list[gw], src, dst, a, nrec, nrow, rbase, coef, stage);
   } else {
     const int64_t n = *count, G = (int64_t)gridDim.x * WPB;
     for (int64_t k = gw; k < n; k += G)
-      step19_tile<S, NT, INC, PH, MRT, SH>(list[k], src, dst, a, nrec, nrow, rbase, coef, stage);
+      step19_tile<S, NT, INC, PH, MRT, SH, STAGE>(list[k], src, dst, a, nrec, nrow, rbase, coef, stage);
   }
 }
 
@@ -536,8 +545,7 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
   return with_variant(v, phase, shuffle, [&](auto sc, auto wc, auto ic, auto pc, auto mc, auto hc) -> hipError_t {
     constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
     constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
-    auto go = [&](auto kern) {
-      constexpr int lds = W * stage_bytes<S, PH, MRT>();
+    auto go = [&](auto kern, int lds) {
       const hipError_t e = allow_lds(reinterpret_cast<const void *>(kern), lds);
       if (e != hipSuccess) return e;
       hipLaunchKernelGGL(kern, dim3(blocks), dim3(64 * W), lds, s, src, dst, a, nrec, nrow, rbase, coef, list, count);
@@ -545,10 +553,13 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
     };
     auto by_mode = [&](auto nt) {
       constexpr bool NT = decltype(nt)::value;
+      constexpr int lds = W * stage_bytes<S, PH, MRT>();
+      if constexpr (lds != 0)
+        if (mode == kDirect && few_tiles<S>(a.n_waves)) return go(k_step19<S, W, NT, INC, PH, MRT, kFew, SH>, 0);
       switch (mode) {
-        case kDirect: return go(k_step19<S, W, NT, INC, PH, MRT, kDirect, SH>);
-        case kList: return go(k_step19<S, W, NT, INC, PH, MRT, kList, SH>);
-        default: return go(k_step19<S, W, NT, INC, PH, MRT, kPersistent, SH>);
+        case kDirect: return go(k_step19<S, W, NT, INC, PH, MRT, kDirect, SH>, lds);
+        case kList: return go(k_step19<S, W, NT, INC, PH, MRT, kList, SH>, lds);
+        default: return go(k_step19<S, W, NT, INC, PH, MRT, kPersistent, SH>, lds);
       }
     };
     // MRT is built with non-temporal stores only (the planner rejects others)
