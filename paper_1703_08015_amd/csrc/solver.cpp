@@ -377,7 +377,6 @@ struct lbm_solver {
   // captured graphs of graph_steps steps, one per starting copy
   hipStream_t cap_stream = nullptr;
   hipGraphExec_t graph[2] = {nullptr, nullptr};
-  int graph_end[2] = {0, 0};  // the copy (layout) a graph ends in
   bool scalar_mask = false;  // which step kernel runs
   bool shuffle = false;      // the scalar-mask kernel in its shuffle form
   double *part = nullptr, *chunk = nullptr, *out = nullptr, *uref = nullptr;
@@ -728,24 +727,26 @@ extern "C" int lbm_init(lbm_solver *s, const double *rho, const double *u) {
   return LBM_OK;
 }
 
-// Enqueue one launch of at most n > 0 steps from copy (two copies) or layout
-// (single copy) `from` on `st`; *done: the steps it takes.  The state is then
-// in the other copy (layout).
-static hipError_t enqueue_step(lbm_solver *s, int from, int n, hipStream_t st, int *done) {
+// Launches for n > 0 steps, as many as n modulo 2.
+static int step_launches(const lbm_solver *s, int n) {
+  if (s->single_copy || s->n_samples != 1 || (s->args.lid.axis >= 0 && s->n_lid_tiles > 0)) return n;
+  return lbm::steps9_launches(s->var, s->samples_h[0].shape, s->args.n_waves, n);
+}
+
+// Enqueue one launch of k steps (1, unless step_launches asked for fewer
+// launches) from copy (two copies) or layout (single copy) `from` on `st`.  The
+// state is then in the other copy (layout).
+static hipError_t enqueue_step(lbm_solver *s, int from, int k, hipStream_t st) {
   const int phase = !s->single_copy ? lbm::kPhaseTwoCopy : (from == 0 ? lbm::kPhaseAAGather : lbm::kPhaseAALocal);
-  *done = 1;
+  if (k > 1) {
+    const lbm::SampleRec &S = s->samples_h[0];
+    return lbm::launch_steps9(s->var, s->buf[from], s->buf[from ^ 1], s->args, s->mesh, S.shape, S.tgrid,
+                              s->periodic[0], k, s->omega, st);
+  }
   if (s->args.lid.axis >= 0 && s->n_lid_tiles > 0) {
     const hipError_t e =
         lbm::launch_lid_fixup(s->var, s->buf[from], s->args, s->lid_tiles_d, s->n_lid_tiles, s->single_copy, st);
     if (e != hipSuccess) return e;
-  } else if (!s->single_copy && s->n_samples == 1) {
-    const lbm::SampleRec &S = s->samples_h[0];
-    const int k = lbm::steps9_per_launch(s->var, S.shape, s->args.n_waves, n);
-    if (k > 1) {
-      *done = k;
-      return lbm::launch_steps9(s->var, s->buf[from], s->buf[from ^ 1], s->args, s->mesh, S.shape, S.tgrid,
-                                s->periodic[0], k, s->omega, st);
-    }
   }
   if (s->scalar_mask) {
     const int mode = s->p.persistent ? 2 : (s->all_active ? 0 : 1);
@@ -763,9 +764,12 @@ static int capture(lbm_solver *s, int from) {
   HIP_TRY(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   int c = from;
-  for (int k = 0, done = 0; k < s->p.graph_steps && e == hipSuccess; k += done) {
-    e = enqueue_step(s, c, s->p.graph_steps - k, s->cap_stream, &done);
+  int n = s->p.graph_steps;
+  for (int left = step_launches(s, n); left > 0 && e == hipSuccess; --left) {
+    const int k = n / left + (n % left != 0);
+    e = enqueue_step(s, c, k, s->cap_stream);
     c ^= 1;
+    n -= k;
   }
   hipGraph_t g = nullptr;
   const hipError_t e2 = hipStreamEndCapture(s->cap_stream, &g);
@@ -773,7 +777,6 @@ static int capture(lbm_solver *s, int from) {
   if (e == hipSuccess) e = hipGraphInstantiate(&s->graph[from], g, nullptr, nullptr, 0);
   if (g) (void)hipGraphDestroy(g);
   if (e != hipSuccess) return set_error(LBM_ERR_HIP, "lbm_step: graph capture failed: %s", hipGetErrorString(e));
-  s->graph_end[from] = c;
   return LBM_OK;
 }
 
@@ -789,15 +792,17 @@ extern "C" int lbm_step(lbm_solver *s, int32_t n) {
         if (rc) return rc;
       }
       HIP_TRY(hipGraphLaunch(s->graph[s->cur], s->stream));
-      s->cur = s->graph_end[s->cur];
+      s->cur ^= (K & 1);
       s->steps += K;
       n -= K;
     }
   }
-  for (int done = 0; n > 0; n -= done) {
-    HIP_TRY(enqueue_step(s, s->cur, n, s->stream, &done));
+  for (int left = n > 0 ? step_launches(s, n) : 0; left > 0; --left) {
+    const int k = n / left + (n % left != 0);
+    HIP_TRY(enqueue_step(s, s->cur, k, s->stream));
     s->cur ^= 1;
-    s->steps += done;
+    s->steps += k;
+    n -= k;
   }
   return LBM_OK;
 }

@@ -144,14 +144,17 @@ int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * 
 
 }  // namespace
 
-// Steps of the next launch when n more are wanted; 1: the single step.  Eight
-// where the windows of eight steps are no more than the compute units, so that
-// all run at once and a step costs its latency; else four, where the doubled
-// layers weigh less.  One sweep over the steps per launch, FP64, us per step:
+// Launches for n steps (n: single steps).  Eight steps per launch where the
+// windows of eight steps are no more than the compute units, so that all run
+// at once and a step costs its latency; else four, where the doubled layers
+// weigh less.  One sweep over the steps per launch, FP64, us per step:
 //   256x256: 4.4 by one, 2.7 by four, 2.0 by eight;
 //   512x512: 7.5 by one, 4.5 by four, 5.4 by five, 5.5 by eight;
 //   4096x4096: 416 by one, 326 by two, 253 by four, 255 by five, 316 by eight.
-// What is left over is spread evenly (ten steps as 4 + 3 + 3).  Single steps
+// The launches are as many as n modulo 2, so that n steps leave the state in
+// the copy where n single steps leave it: a caller that captured an even
+// number of steps replays them from the copy they end in.  The steps are
+// spread evenly over them (ten steps by four: 3 + 3 + 2 + 2).  Single steps
 // stay for
 //  - two steps of FP32 on larger grids (1536x1500: 25.5 us per step by two,
 //    24.7 by one),
@@ -159,14 +162,16 @@ int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * 
 //    FP64 41.7 us by one, 49.0 by four; FP32 28.0 and 28.4),
 //  - geometries with fewer than one tile for every four windows, where most of
 //    a launch would look at solid nodes.
-int steps9_per_launch(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
-  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1) return 1;
+int steps9_launches(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1) return n;
   const bool small = (int64_t)windows(shape[0], 8) * windows(shape[1], 8) <= 256;
-  if (!small && v.collision == LBM_COLLISION_MRT) return 1;
-  const int most = small ? 8 : 4, launches = n / most + (n % most != 0);
+  if (!small && v.collision == LBM_COLLISION_MRT) return n;
+  const int most = small ? 8 : 4;
+  int launches = n / most + (n % most != 0);
+  launches += (launches ^ n) & 1;
   const int k = n / launches + (n % launches != 0);
-  if (!small && k == 2 && v.storage != LBM_F64) return 1;
-  return (int64_t)windows(shape[0], k) * windows(shape[1], k) <= n_waves ? k : 1;
+  if (k == 1 || (!small && k == 2 && v.storage != LBM_F64)) return n;
+  return (int64_t)windows(shape[0], k) * windows(shape[1], k) <= n_waves ? launches : n;
 }
 
 hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const TileArgs &a, const MeshArgs &m,
