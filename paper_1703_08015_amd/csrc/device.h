@@ -414,27 +414,29 @@ constexpr double mrt_src_C(int k, int a, int b) {
 
 template <class L, int K, class R>
 __device__ __forceinline__ R mrt_source_moment(R m, const R (&u)[3], const R (&g)[3], R ug) {
+  // explicit fma and no other contraction, as in collide_mrt
+#pragma clang fp contract(off)
   R acc = R(0);
   bool any = false;
-  auto add = [&](R term) {
-    acc = any ? acc + term : term;
+  auto add = [&](R c, R v) {
+    acc = any ? std::fma(c, v, acc) : c * v;
     any = true;
   };
   static_for<3>([&](auto A) {
     constexpr int a = decltype(A)::value;
     constexpr double ca = 3.0 * mrt_src_A<L>(K, a);
-    if constexpr (ca != 0.0) add(R(ca) * g[a]);
+    if constexpr (ca != 0.0) add(R(ca), g[a]);
   });
   {
     constexpr double cb = -3.0 * mrt_src_B<L>(K);
-    if constexpr (cb != 0.0) add(R(cb) * ug);
+    if constexpr (cb != 0.0) add(R(cb), ug);
   }
   static_for<3>([&](auto A) {
     constexpr int a = decltype(A)::value;
     static_for<3>([&](auto B) {
       constexpr int b = decltype(B)::value;
       constexpr double cc = 9.0 * mrt_src_C<L>(K, a, b);
-      if constexpr (cc != 0.0) add(R(cc) * (u[a] * g[b]));
+      if constexpr (cc != 0.0) add(R(cc), u[a] * g[b]);
     });
   });
   return any ? m * acc : R(0);
