@@ -576,13 +576,11 @@ __device__ __forceinline__ BgkRate<L, R> bgk_rate(R om, R gx, R gy, R gz) {
 // with m the density of the velocity terms (the density, or 1) and c0 the density
 // or its offset.  What rounding does to the sum of a node's f* moves mass at every
 // step, which a long run collects: poly is therefore summed before the 1 joins it
-// (else the 64x64 FP64 channel ends with 2e-14 of flow across), and as the weights
-// as doubles sum to 1 - 2^-54 on both lattices, the FP64 quasi-compressible rest
-// weight is the next double, which makes the sum exact (else the velocity never
-// stops changing by 1e-13 in 2000 steps; with it, 3e-15).  The incompressible form
-// keeps the plain weights: its density is checked to 1e-13 after 1000 steps against
-// the dense code, which loses 0.8e-13 by them.  Every multiply-add is an explicit fma and nothing
-// else is contracted, so every kernel that calls it rounds the same way.
+// (summed from the 1 on, the 64x64 FP64 channel ends with 2e-14 of flow across).
+// The weights as doubles sum to 1 - 2^-54 on both lattices and are used as they
+// are, in every kernel, collision and model: a step loses about w 2^-54 of the
+// mass.  Every multiply-add is an explicit fma and nothing else is contracted, so
+// every kernel that calls it rounds the same way.
 template <class L, int S, bool INC, class R>
 __device__ __forceinline__ void collide_bgk(R (&f)[L::Q], R sum, R jx, R jy, R jz, R rho0, const BgkRate<L, R> &k) {
 #pragma clang fp contract(off)
@@ -605,7 +603,7 @@ __device__ __forceinline__ void collide_bgk(R (&f)[L::Q], R sum, R jx, R jy, R j
     if constexpr (product) return std::fma(w * rho, R(1) + poly, -fi);
     else return std::fma(w, std::fma(m, poly, off ? sum : rho), -fi);
   };
-  constexpr R w0 = R(product ? L::Wt[0] + 0x1p-54 : L::Wt[0]);
+  constexpr R w0 = R(L::Wt[0]);
   f[0] = std::fma(w0 * m, F0, std::fma(k.om, diff(w0, P0, f[0]), f[0]));
   static_for<L::Q / 2>([&](auto I) {
     constexpr int p = decltype(I)::value, i = 2 * p + 1;
