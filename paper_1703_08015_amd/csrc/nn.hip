@@ -11,6 +11,7 @@
 #include <algorithm>
 #include <cmath>
 #include <initializer_list>
+#include <type_traits>
 
 #include "device.h"
 #include "internal.h"
@@ -1524,52 +1525,98 @@ __global__ void k_dist_init(int64_t n, const uint8_t *solid, float *d) {
     d[e] = solid[e] ? 0.f : kFar;
 }
 
-// Four sweeps per launch on bricks of at most 16^3 nodes: the brick and the
-// four nodes around it go to LDS, where the sweeps run; the outermost layer is
-// left as it is, so what is wrong moves in by one node a sweep and stops at
-// the brick.  Each sweep reads every value before it writes any (the results
-// are those of sweeps over the whole grid, bit for bit, whatever their count).
-// A thread owns four nodes in x of six z-layers and marches up z: a layer's
-// nodes are read once (nine 4-node reads per layer), for the minimum over the
-// layer itself and for what it offers to the layers above and below.
+// One sweep over the grid.
+__global__ void __launch_bounds__(256) k_dist_sweep(Grid g, uint32_t periodic, const uint8_t *solid,
+                                                    const float *din, float *dout) {
+  const int64_t n = (int64_t)g.nx * g.ny * g.nz;
+  const int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (e >= n) return;
+  if (solid[e]) {
+    dout[e] = 0.f;
+    return;
+  }
+  const int x = (int)(e % g.nx), y = (int)((e / g.nx) % g.ny), z = (int)(e / ((int64_t)g.nx * g.ny));
+  float best = din[e];
+  lbm::static_for<19>([&](auto i) {
+    constexpr int cx = lbm::D3Q19::C[i][0], cy = lbm::D3Q19::C[i][1], cz = lbm::D3Q19::C[i][2];
+    if constexpr (cx != 0 || cy != 0 || cz != 0) {
+      constexpr float len = ((cx != 0) + (cy != 0) + (cz != 0)) == 1 ? 1.0f : 1.41421356237309515f;
+      int tx = x + cx, ty = y + cy, tz = z + cz;
+      bool inside = true;
+      if (tx < 0 || tx >= g.nx) {
+        inside &= (periodic & 1u) != 0;
+        tx = tx < 0 ? tx + g.nx : tx - g.nx;
+      }
+      if (ty < 0 || ty >= g.ny) {
+        inside &= (periodic & 2u) != 0;
+        ty = ty < 0 ? ty + g.ny : ty - g.ny;
+      }
+      if (tz < 0 || tz >= g.nz) {
+        inside &= (periodic & 4u) != 0;
+        tz = tz < 0 ? tz + g.nz : tz - g.nz;
+      }
+      if (inside) best = fminf(best, din[vidx(tx, ty, tz, g)] + len);
+    }
+  });
+  dout[e] = best;
+}
+
+// Four sweeps per launch on bricks: the brick and the four nodes around it go
+// to LDS, where the sweeps run; the outermost layer is left as it is, so what
+// is wrong moves in by one node a sweep and stops at the brick.  Each sweep
+// reads every value before it writes any (the results are those of sweeps over
+// the whole grid, bit for bit, whatever their count).  A thread owns four nodes
+// in x of LZ z-layers and marches up z: a layer's nodes are read once (nine
+// 4-node reads per layer), for the minimum over the layer itself and for what
+// it offers to the layers above and below.
 // A brick whose own and neighbouring values did not change in the launch
 // before is done: it keeps its values (both buffers hold them).  The sign bit
 // of its first value carries "changed" to the next launch; the last launch
-// clears it.  128^3 at porosity 0.5, 64 sweeps: 1770 us for one launch per
-// sweep (27 us each, 18 neighbour loads per node), 390 us so (77 us a launch
-// while most bricks change, bound by vector instructions; 5 us once all are
-// done).
-constexpr int kDistSweeps = 4, kDistBrick = 16, kDistRegion = kDistBrick + 2 * kDistSweeps;  // 24
-constexpr int kDistLayers = 6;
-constexpr int kDistThreads = kDistRegion / 4 * kDistRegion * (kDistRegion / kDistLayers);  // 576
+// clears it.  128^3 at porosity 0.5, 64 sweeps: 1720 us by single sweeps, 282 us
+// so (74 us a launch while all bricks change, bound by vector instructions; 5 us
+// once all are done).
+constexpr int kDistSweeps = 4;
 
-// Bricks of an axis: n split into ceil(n / 16) pieces of nearly equal length
-// (at least 8 where there is more than one, so a halo of 4 ends in the next).
-__device__ __forceinline__ int dist_bricks(int n) { return (n + kDistBrick - 1) / kDistBrick; }
-__device__ __forceinline__ int dist_begin(int b, int n) {
-  const int nb = dist_bricks(n), rem = n % nb;
+// Brick of at most BX x BY x BZ nodes; a 2D brick (BZ = 1) is for grids of one
+// layer, whose links along z never give less than those in the layer.
+template <int BX, int BY, int BZ, int LZ>
+struct DistBrick {
+  static constexpr bool flat = BZ == 1;
+  static constexpr int H = kDistSweeps, B[3] = {BX, BY, BZ}, R[3] = {BX + 2 * H, BY + 2 * H, flat ? 1 : BZ + 2 * H};
+  static constexpr int layers = LZ, threads = R[0] / 4 * R[1] * (R[2] / LZ);
+  static_assert(R[0] % 4 == 0 && R[2] % LZ == 0 && threads <= 1024);
+};
+
+// Bricks of an axis: n split into pieces of nearly equal length, at least half
+// of B where there is more than one (so that a halo of 4 ends in the next: B is
+// at least 8 then).
+__device__ __host__ __forceinline__ int dist_bricks(int n, int B) { return (n + B - 1) / B; }
+__device__ __forceinline__ int dist_begin(int b, int n, int B) {
+  const int nb = dist_bricks(n, B), rem = n % nb;
   return b * (n / nb) + (b < rem ? b : rem);
 }
 
-__global__ void __launch_bounds__(kDistThreads, 5)
+template <class K>
+__global__ void __launch_bounds__(K::threads, 5)
     k_dist_sweeps(Grid g, uint32_t periodic, const uint8_t *solid, const float *din, float *dout, int sweeps, int skip,
                   int last) {
   // one layer, one row and one node of padding at either end: the outermost
   // nodes' reads past the region stay in the array (what they give reaches
   // only values that are not kept), so every read is a constant offset away
-  constexpr int kRow = kDistRegion, kLayer = kDistRegion * kDistRegion, kPad = (kLayer + kRow + 1 + 7) / 8 * 8;
-  __shared__ __attribute__((aligned(16))) float d_s[kPad + kDistRegion * kLayer + kPad];
+  constexpr int H = K::H, LZ = K::layers, RX = K::R[0], RY = K::R[1], RZ = K::R[2];
+  constexpr int kRow = RX, kLayer = RX * RY, kPad = ((K::flat ? 0 : kLayer) + kRow + 1 + 7) / 8 * 8;
+  __shared__ __attribute__((aligned(16))) float d_s[kPad + RZ * kLayer + kPad];
   __shared__ int busy;
   float *const d = d_s + kPad;
   const int n[3] = {g.nx, g.ny, g.nz};
-  const int nb[3] = {dist_bricks(g.nx), dist_bricks(g.ny), dist_bricks(g.nz)};
+  const int nb[3] = {dist_bricks(g.nx, K::B[0]), dist_bricks(g.ny, K::B[1]), dist_bricks(g.nz, K::B[2])};
   const int blk[3] = {(int)(blockIdx.x % nb[0]), (int)(blockIdx.x / nb[0] % nb[1]),
                       (int)(blockIdx.x / ((unsigned)nb[0] * nb[1]))};
   int o[3], len[3];  // the brick
 #pragma unroll
   for (int a = 0; a < 3; ++a) {
-    o[a] = dist_begin(blk[a], n[a]);
-    len[a] = dist_begin(blk[a] + 1, n[a]) - o[a];
+    o[a] = dist_begin(blk[a], n[a], K::B[a]);
+    len[a] = dist_begin(blk[a] + 1, n[a], K::B[a]) - o[a];
   }
   const int tid = threadIdx.x;
   const int64_t corner = vidx(o[0], o[1], o[2], g);
@@ -1584,7 +1631,8 @@ __global__ void __launch_bounds__(kDistThreads, 5)
         there = there && ((periodic >> a) & 1u);
         q[a] = q[a] < 0 ? nb[a] - 1 : 0;
       }
-    if (there && signbit(din[vidx(dist_begin(q[0], n[0]), dist_begin(q[1], n[1]), dist_begin(q[2], n[2]), g)]))
+    if (there && signbit(din[vidx(dist_begin(q[0], n[0], K::B[0]), dist_begin(q[1], n[1], K::B[1]),
+                                  dist_begin(q[2], n[2], K::B[2]), g)]))
       busy = 1;
   }
   __syncthreads();
@@ -1592,18 +1640,19 @@ __global__ void __launch_bounds__(kDistThreads, 5)
     if (tid == 0) dout[corner] = fabsf(din[corner]);
     return;
   }
+  // nodes of the halo below the brick along an axis
+  auto halo = [](int a) { return a == 2 && K::flat ? 0 : H; };
   // a region coordinate's node along an axis (wrapped), -1 past a wall
   auto node = [&](int a, int l) -> int {
-    int v = o[a] - kDistSweeps + l;
+    int v = o[a] - halo(a) + l;
     if (v >= 0 && v < n[a]) return v;
     if (!((periodic >> a) & 1u)) return -1;
     v %= n[a];
     return v < 0 ? v + n[a] : v;
   };
 #pragma unroll 4
-  for (int e = tid; e < kDistRegion * kDistRegion * kDistRegion; e += kDistThreads) {
-    const int x = node(0, e % kDistRegion), y = node(1, e / kDistRegion % kDistRegion),
-              z = node(2, e / (kDistRegion * kDistRegion));
+  for (int e = tid; e < RX * RY * RZ; e += K::threads) {
+    const int x = node(0, e % RX), y = node(1, e / RX % RY), z = node(2, e / (RX * RY));
     float v = kFar;
     if (x >= 0 && y >= 0 && z >= 0) {
       const int64_t i = vidx(x, y, z, g);
@@ -1612,27 +1661,26 @@ __global__ void __launch_bounds__(kDistThreads, 5)
     d[e] = v;
   }
   __syncthreads();
-  const int x0 = 4 * (tid % (kDistRegion / 4)), y = tid / (kDistRegion / 4) % kDistRegion,
-            z0 = kDistLayers * (tid / (kDistRegion / 4 * kDistRegion));
+  const int x0 = 4 * (tid % (RX / 4)), y = tid / (RX / 4) % RY, z0 = LZ * (tid / (RX / 4 * RY));
   // nodes this thread may change: inside the region's outermost layer and the walls
-  bool xy_ok[4], z_ok[kDistLayers];
+  bool xy_ok[4], z_ok[LZ];
   auto free = [&](int a, int l) {
-    const int v = o[a] - kDistSweeps + l;
-    return l > 0 && l < kDistRegion - 1 && (((periodic >> a) & 1u) || (v >= 0 && v < n[a]));
+    if (a == 2 && K::flat) return true;
+    const int v = o[a] - H + l;
+    return l > 0 && l < K::R[a] - 1 && (((periodic >> a) & 1u) || (v >= 0 && v < n[a]));
   };
 #pragma unroll
   for (int k = 0; k < 4; ++k) xy_ok[k] = free(0, x0 + k) && free(1, y);
 #pragma unroll
-  for (int l = 0; l < kDistLayers; ++l) z_ok[l] = free(2, z0 + l);
+  for (int l = 0; l < LZ; ++l) z_ok[l] = free(2, z0 + l);
   float *const mine = d + x0 + kRow * y + kLayer * z0;
   constexpr float kDiag = 1.41421356237309515f;
   // nodes whose change makes the brick (and so its neighbours) work on
-  bool x_in[4], z_in[kDistLayers];
+  bool x_in[4], z_in[LZ];
 #pragma unroll
-  for (int k = 0; k < 4; ++k)
-    x_in[k] = x0 + k >= kDistSweeps && x0 + k < kDistSweeps + len[0] && y >= kDistSweeps && y < kDistSweeps + len[1];
+  for (int k = 0; k < 4; ++k) x_in[k] = x0 + k >= H && x0 + k < H + len[0] && y >= H && y < H + len[1];
 #pragma unroll
-  for (int l = 0; l < kDistLayers; ++l) z_in[l] = z0 + l >= kDistSweeps && z0 + l < kDistSweeps + len[2];
+  for (int l = 0; l < LZ; ++l) z_in[l] = z0 + l >= halo(2) && z0 + l < halo(2) + len[2];
   // distances are not negative, so they order as their bits do (and the
   // minimum of integers needs no care for signalling NaNs)
   auto lower = [](float a, float b) {
@@ -1641,9 +1689,9 @@ __global__ void __launch_bounds__(kDistThreads, 5)
   bool changed = false;
   for (int s = 0; s < sweeps; ++s) {
     // offered by the layer below; the layer's own minimum and its old values
-    float fresh[kDistLayers][4], below[4], here[4], old[4];
+    float fresh[LZ][4], below[4], here[4], old[4];
 #pragma unroll
-    for (int l = -1; l <= kDistLayers; ++l) {
+    for (int l = K::flat ? 0 : -1; l <= (K::flat ? 0 : LZ); ++l) {
       float row[3][6];
 #pragma unroll
       for (int r = 0; r < 3; ++r) {
@@ -1658,13 +1706,18 @@ __global__ void __launch_bounds__(kDistThreads, 5)
         const float c = row[1][k + 1];
         const float face = lower(lower(row[1][k], row[1][k + 2]), lower(row[0][k + 1], row[2][k + 1]));
         const float diag = lower(lower(row[0][k], row[0][k + 2]), lower(row[2][k], row[2][k + 2]));
+        if constexpr (K::flat) {
+          fresh[0][k] = xy_ok[k] ? lower(c, lower(face + 1.f, diag + kDiag)) : c;
+          changed |= fresh[0][k] < c && x_in[k];
+          continue;
+        }
         const float offer = lower(c + 1.f, face + kDiag);
         if (l > 0) {
           const bool ok = z_ok[l - 1] && xy_ok[k];
           fresh[l - 1][k] = ok ? lower(here[k], offer) : old[k];
           changed |= fresh[l - 1][k] < old[k] && z_in[l - 1] && x_in[k];
         }
-        if (l >= 0 && l < kDistLayers) here[k] = lower(lower(c, below[k]), lower(face + 1.f, diag + kDiag));
+        if (l >= 0 && l < LZ) here[k] = lower(lower(c, below[k]), lower(face + 1.f, diag + kDiag));
         below[k] = offer;
         old[k] = c;
       }
@@ -1672,15 +1725,15 @@ __global__ void __launch_bounds__(kDistThreads, 5)
     }
     __syncthreads();  // every read of this sweep is done
 #pragma unroll
-    for (int l = 0; l < kDistLayers; ++l)
+    for (int l = 0; l < LZ; ++l)
       *reinterpret_cast<float4 *>(mine + kLayer * l) =
           make_float4(fresh[l][0], fresh[l][1], fresh[l][2], fresh[l][3]);
     __syncthreads();
   }
   const bool mark = __syncthreads_or(changed || !din) && !last;
-  for (int e = tid; e < len[0] * len[1] * len[2]; e += kDistThreads) {
+  for (int e = tid; e < len[0] * len[1] * len[2]; e += K::threads) {
     const int x = e % len[0], yy = e / len[0] % len[1], z = e / (len[0] * len[1]);
-    float v = d[x + kDistSweeps + kRow * (yy + kDistSweeps) + kLayer * (z + kDistSweeps)];
+    float v = d[x + H + kRow * (yy + H) + kLayer * (z + halo(2))];
     if (mark && e == 0) v = -v;
     dout[vidx(o[0] + x, o[1] + yy, o[2] + z, g)] = v;
   }
@@ -2404,6 +2457,55 @@ extern "C" int lbm_nn_encode_input(int64_t n, const uint8_t *solid, const float 
   return LBM_OK;
 }
 
+// How the distance sweeps run: on 16^3, 8^3 or 2D bricks, or one launch per sweep.
+namespace {
+using DistCube = DistBrick<16, 16, 16, 6>;
+using DistSmall = DistBrick<8, 8, 8, 4>;
+using DistFlat = DistBrick<32, 32, 1, 1>;
+
+template <class K>
+int64_t dist_grid(const Grid &g) {
+  return (int64_t)dist_bricks(g.nx, K::B[0]) * dist_bricks(g.ny, K::B[1]) * dist_bricks(g.nz, K::B[2]);
+}
+
+// The form with the least time by these measures (us), on geometries between a
+// random 60% and one solid node.  A launch of four sweeps over b bricks that all
+// work: 16^3 bricks 37 for every 256 (576 threads and 60 KB of LDS, so twice the
+// bricks at once take twice as long), 8^3 bricks 12 + 0.021 b, 2D bricks
+// 6 + 0.0105 b; of two sweeps 0.7 of that.  From the third launch on most bricks
+// are done: 3 + 0.0013 b.  A single sweep: 5.3, and 4 + 13e-6 per node on larger
+// grids.  What it decides, 64 / 8 / 2 sweeps, single sweeps : 16^3 : 8^3 : 2D,
+//   32^3         356 / 49 / 19 : 121 / 77 / 27 : 78 / 30 / 12
+//   64^3         418 / 58 / 18 : 118 / 75 / 27 : 89 / 43 / 15
+//   128^3        1715 / 229 / 63 : 212 / 146 / 51 : 290 / 191 / 59
+//   4 x 512^2    1186 / 158 / 43 : 366 / 261 / 93 : 291 / 188 / 57
+//   1 x 512^2    523 / 71 / 20 : 361 / 257 / 91 : 283 / 183 / 56 : 64 / 17 / 8.4
+//   1500 x 1536  2226 / 290 / 79 : 2915 / 2164 / 750 : 2106 / 1459 / 413 : 155 / 61 / 24
+template <class F>
+void with_dist_form(const Grid &g, int sweeps, F &&run) {
+  const double n = (double)g.nx * g.ny * g.nz;
+  const int launches = (sweeps + kDistSweeps - 1) / kDistSweeps;
+  const int64_t cubes = dist_grid<DistCube>(g), small = dist_grid<DistSmall>(g), flat = dist_grid<DistFlat>(g);
+  auto total = [&](auto brick, int64_t b, double launch) {
+    if (b * decltype(brick)::threads > (int64_t)UINT32_MAX) return INFINITY;
+    const double full = sweeps <= 2 ? 0.7 : std::min(launches, 2);
+    return (float)(launch * full + std::max(launches - 2, 0) * (3.0 + 0.0013 * b));
+  };
+  const float by_cube = total(DistCube{}, cubes, 37.0 * ((cubes + 255) / 256)),
+              by_small = total(DistSmall{}, small, 12.0 + 0.021 * small),
+              by_flat = g.nz == 1 ? total(DistFlat{}, flat, 6.0 + 0.0105 * flat) : INFINITY;
+  const float single = (float)(5.0 + sweeps * std::max(5.3, 4.0 + 13e-6 * n));
+  if (sweeps == 0 || single <= std::min(by_cube, std::min(by_small, by_flat)))
+    run(nullptr, 0);
+  else if (by_flat <= std::min(by_cube, by_small))
+    run(DistFlat{}, flat);
+  else if (by_small <= by_cube)
+    run(DistSmall{}, small);
+  else
+    run(DistCube{}, cubes);
+}
+}  // namespace
+
 extern "C" int lbm_nn_distance(const int32_t shape[3], uint32_t periodic, const uint8_t *solid, int32_t sweeps,
                                float *dist, float *tmp, void *stream) {
   if (!shape || !solid || !dist || !tmp || dist == tmp) return set_error(LBM_ERR_ARG, "lbm_nn_distance: args");
@@ -2413,17 +2515,26 @@ extern "C" int lbm_nn_distance(const int32_t shape[3], uint32_t periodic, const 
   const Grid g{shape[0], shape[1], shape[2]};
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (sweeps == 0) hipLaunchKernelGGL(k_dist_init, dim3(grid_for(n)), dim3(256), 0, s, n, solid, dist);
-  auto bricks = [](int v) { return (int64_t)((v + kDistBrick - 1) / kDistBrick); };
-  const unsigned grid = (unsigned)(bricks(g.nx) * bricks(g.ny) * bricks(g.nz));
-  // pairs of sweeps, four to a launch; the last launch ends in dist
-  const int total = (sweeps + 1) / 2 * 2, launches = (total + kDistSweeps - 1) / kDistSweeps;
-  for (int k = 0; k < launches; ++k) {
-    float *out = (launches - k) % 2 ? dist : tmp;
-    const float *in = k == 0 ? nullptr : (out == dist ? tmp : dist);
-    hipLaunchKernelGGL(k_dist_sweeps, dim3(grid), dim3(kDistThreads), 0, s, g, periodic, solid, in, out,
-                       std::min(kDistSweeps, total - kDistSweeps * k), k >= 2 ? 1 : 0, k + 1 == launches ? 1 : 0);
-  }
+  with_dist_form(g, sweeps, [&](auto brick, int64_t bricks) {
+    using K = decltype(brick);
+    if constexpr (std::is_same_v<K, std::nullptr_t>) {
+      hipLaunchKernelGGL(k_dist_init, dim3(grid_for(n)), dim3(256), 0, s, n, solid, dist);
+      const unsigned grid = (unsigned)((n + 255) / 256);
+      for (int k = 0; k < (sweeps + 1) / 2; ++k) {  // pairs of sweeps end in dist
+        hipLaunchKernelGGL(k_dist_sweep, dim3(grid), dim3(256), 0, s, g, periodic, solid, (const float *)dist, tmp);
+        hipLaunchKernelGGL(k_dist_sweep, dim3(grid), dim3(256), 0, s, g, periodic, solid, (const float *)tmp, dist);
+      }
+    } else {
+      // pairs of sweeps, four to a launch; the last launch ends in dist
+      const int total = (sweeps + 1) / 2 * 2, launches = (total + kDistSweeps - 1) / kDistSweeps;
+      for (int k = 0; k < launches; ++k) {
+        float *out = (launches - k) % 2 ? dist : tmp;
+        const float *in = k == 0 ? nullptr : (out == dist ? tmp : dist);
+        hipLaunchKernelGGL(k_dist_sweeps<K>, dim3((unsigned)bricks), dim3(K::threads), 0, s, g, periodic, solid, in, out,
+                           std::min(kDistSweeps, total - kDistSweeps * k), k >= 2 ? 1 : 0, k + 1 == launches ? 1 : 0);
+      }
+    }
+  });
   NN_TRY(hipGetLastError());
   return LBM_OK;
 }
