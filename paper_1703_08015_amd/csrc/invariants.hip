@@ -150,9 +150,14 @@ static_assert(kSx * kSy * kSz == 4 * kBlock && kHx <= 32, "four nodes per thread
 // fields; the last one writes u.
 enum SweepEnds : int { kInner = 0, kFirst = 1, kLast = 2 };
 
-// rho u, rounded once where r starts and where u is formed, so that a node no
-// link reaches (r = rho u to the end) comes out at rest exactly
+// rho u, rounded once where r starts and where u is formed, so that a component
+// no link carries keeps r = rho u to the end, in every bit, and comes out as 0,
+// also where it is infinite or NaN (where `times` keeps it from the others)
 __device__ __forceinline__ double momentum(double rho, double u) { return __dmul_rn(rho, u); }
+__device__ __forceinline__ double kept(double momentum, double r) {
+  return __double_as_longlong(momentum) == __double_as_longlong(r) ? 0.0 : momentum - r;
+}
+__device__ __forceinline__ double times(int count, double r) { return count != 0 ? count * r : 0.0; }
 
 template <class L, int ENDS>
 __global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t *lab, int32_t count,
@@ -206,6 +211,7 @@ __global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t
       continue;
     }
     const double r0[3] = {rs[0][c0], rs[1][c0], rs[2][c0]};
+    const bool finite = __builtin_isfinite(r0[0]) && __builtin_isfinite(r0[1]) && __builtin_isfinite(r0[2]);
     double acc[3] = {0.0, 0.0, 0.0};  // 2/3 T r, weight by weight
     lbm::static_for<2>([&](auto Cls) {
       constexpr bool edge = decltype(Cls)::value == 1;  // links with two nonzero components, or one
@@ -232,15 +238,21 @@ __global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t
           if constexpr (cx * cy != 0) off[2] += cx * cy * b;
         }
       });
-      s[0] += diag[0] * r0[0] + off[2] * r0[1] + off[1] * r0[2];
-      s[1] += off[2] * r0[0] + diag[1] * r0[1] + off[0] * r0[2];
-      s[2] += off[1] * r0[0] + off[0] * r0[1] + diag[2] * r0[2];
+      if (finite) {
+        s[0] += diag[0] * r0[0] + off[2] * r0[1] + off[1] * r0[2];
+        s[1] += off[2] * r0[0] + diag[1] * r0[1] + off[0] * r0[2];
+        s[2] += off[1] * r0[0] + off[0] * r0[1] + diag[2] * r0[2];
+      } else {
+        s[0] += times(diag[0], r0[0]) + times(off[2], r0[1]) + times(off[1], r0[2]);
+        s[1] += times(off[2], r0[0]) + times(diag[1], r0[1]) + times(off[0], r0[2]);
+        s[2] += times(off[1], r0[0]) + times(off[0], r0[1]) + times(diag[2], r0[2]);
+      }
       constexpr double w = 1.5 * L::Wt[edge ? L::Q - 1 : 1];
       for (int k = 0; k < 3; ++k) acc[k] += w * s[k];
     });
     if constexpr (ENDS & kLast) {
       const double m = rho[i];
-      for (int k = 0; k < 3; ++k) u[k * n + i] = (momentum(m, u[k * n + i]) - (r0[k] - acc[k])) / m;
+      for (int k = 0; k < 3; ++k) u[k * n + i] = kept(momentum(m, u[k * n + i]), r0[k] - acc[k]) / m;
     } else {
       for (int k = 0; k < 3; ++k) r_out[k * n + i] = r0[k] - acc[k];
     }
@@ -253,7 +265,7 @@ __global__ void __launch_bounds__(kBlock) k_velocity(int64_t n, const int32_t *l
   const int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x;
   if (i >= n || checked(lab[i], count) < 0) return;
   const double m = rho[i];
-  for (int k = 0; k < 3; ++k) u[k * n + i] = (momentum(m, u[k * n + i]) - r[k * n + i]) / m;
+  for (int k = 0; k < 3; ++k) u[k * n + i] = kept(momentum(m, u[k * n + i]), r[k * n + i]) / m;
 }
 
 template <class L>
