@@ -17,11 +17,11 @@
 // Launches on the caller's stream: clear the per-component sums, sum
 // (rho, 1) per component, rescale rho, one stencil launch per sweep
 // (ping-pong buffers in the scratch), the last of which writes u.
-// Per-component sums: a wavefront keeps the component it met first in
-// registers over a stride of nodes and adds any other with cross-lane
-// shuffles, and a workgroup adds one total, so a giant component costs one
-// FP64 atomic pair per workgroup (112 x 104 x 96 at porosity 0.5: 420 -> 16 us
-// against one pair per 64 nodes, all on one address).
+// Per-component sums: a wavefront keeps two components in registers over a stride
+// of nodes, and a workgroup adds one total (112 x 104 x 96 at porosity 0.5: 420 ->
+// 11 us against one FP64 atomic pair per 64 nodes, all on one address; 128^3 with
+// 14,524 pockets in 5% of the nodes: 24 -> 20 us, with 10,080 components in 12%:
+// 700 -> 106 us).
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -37,29 +37,6 @@ namespace {
 constexpr int kBlock = 256;
 constexpr int kMaxIterations = 1000;
 
-// Add (a, b) of every lane to acc[2*label], acc[2*label + 1]; lanes with a
-// negative label add nothing.  Every lane of the wave must call it.
-__device__ inline void wave_add2(double *acc, int label, double a, double b) {
-  unsigned long long pending = __ballot(label >= 0);
-  const int lane = __lane_id();
-  while (pending) {
-    const int leader = __ffsll(pending) - 1;
-    const int L = __shfl(label, leader);
-    const bool mine = label == L;
-    double x = mine ? a : 0.0, y = mine ? b : 0.0;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-      x += __shfl_xor(x, off);
-      y += __shfl_xor(y, off);
-    }
-    if (lane == leader) {
-      unsafeAtomicAdd(acc + 2 * (int64_t)L, x);
-      unsafeAtomicAdd(acc + 2 * (int64_t)L + 1, y);
-    }
-    pending &= ~__ballot(mine);
-  }
-}
-
 // Labels outside [0, count) are treated as solid: a bad label array leaves
 // its nodes untouched instead of adding out of bounds.
 __device__ inline int checked(int32_t label, int32_t count) { return label < count ? label : -1; }
@@ -68,53 +45,97 @@ __global__ void __launch_bounds__(kBlock) k_clear(double *p, int64_t n) {
   for (int64_t i = blockIdx.x * (int64_t)kBlock + threadIdx.x; i < n; i += (int64_t)gridDim.x * kBlock) p[i] = 0.0;
 }
 
-constexpr int kMassBlocks = 256;  // at most one workgroup per compute unit
+// (rho, 1) summed per component.  A wavefront goes over its nodes 64 at a time and
+// holds the sums of two components, per lane, in registers: a, the one that it
+// has met again and again, and b, the largest other one of the last 64 nodes
+// that had neither (which becomes a when it comes again where a does not).  What
+// a further component has (a pocket's few nodes) goes to memory lane by lane, all
+// lanes at once.  At the end the workgroup's wavefronts of one component are
+// added together, so a component that fills the pores gets one atomic pair per
+// workgroup and not one per 64 nodes, all on one address.
+constexpr int kMassThreads = 1024, kMassBlocks = 256;  // one workgroup per compute unit
+constexpr int kManyLanes = 8;  // from here on one atomic pair for a component's lanes
 
-__global__ void __launch_bounds__(kBlock) k_mass(int64_t n, const int32_t *lab, int32_t count, const double *rho,
-                                                 double *acc) {
-  __shared__ int label_s[kBlock / 64];
-  __shared__ double sum_s[kBlock / 64][2];
-  int cur = -1;  // this wavefront's component (uniform), summed per lane
-  double x = 0.0, y = 0.0;
-  const int64_t first = (blockIdx.x * (int64_t)kBlock + threadIdx.x) & ~(int64_t)63;
-  for (int64_t base = first; base < n; base += (int64_t)gridDim.x * kBlock) {
-    const int64_t i = base + __lane_id();
-    const int L = i < n ? checked(lab[i], count) : -1;
-    const double r = L >= 0 ? rho[i] : 0.0;
-    const unsigned long long any = __ballot(L >= 0);
-    if (cur < 0 && any) cur = __shfl(L, __ffsll(any) - 1);
-    const bool mine = L >= 0 && L == cur;
-    if (mine) {
-      x += r;
-      y += 1.0;
-    }
-    if (__ballot(L >= 0 && !mine)) wave_add2(acc, mine ? -1 : L, r, 1.0);
-  }
+__device__ __forceinline__ void add_sums(double *acc, int label, double x, double y) {
+  unsafeAtomicAdd(acc + 2 * (int64_t)label, x);
+  unsafeAtomicAdd(acc + 2 * (int64_t)label + 1, y);
+}
+
+__device__ __forceinline__ void wave_sum2(double &x, double &y) {
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     x += __shfl_xor(x, off);
     y += __shfl_xor(y, off);
   }
-  const int wv = threadIdx.x >> 6;
-  if (__lane_id() == 0) {
-    label_s[wv] = cur;
-    sum_s[wv][0] = x;
-    sum_s[wv][1] = y;
+}
+
+__global__ void __launch_bounds__(kMassThreads) k_mass(int64_t n, const int32_t *lab, int32_t count, const double *rho,
+                                                       double *acc) {
+  constexpr int kWaves = kMassThreads / 64;
+  __shared__ int label_s[kWaves];
+  __shared__ double sum_s[kWaves][2];
+  int a = -1, b = -1;  // (uniform)
+  double ax = 0.0, ay = 0.0, bx = 0.0, by = 0.0;
+  const int lane = __lane_id(), wv = threadIdx.x >> 6;
+  auto give = [&](int label, double x, double y) {  // all lanes' sums, one atomic pair
+    wave_sum2(x, y);
+    if (lane == 0) add_sums(acc, label, x, y);
+  };
+  for (int64_t base = (blockIdx.x * (int64_t)kWaves + wv) * 64; base < n; base += (int64_t)gridDim.x * kMassThreads) {
+    const int64_t i = base + lane;
+    const int L = i < n ? checked(lab[i], count) : -1;
+    const double r = L >= 0 ? rho[i] : 0.0;
+    const bool on = L >= 0, in_a = on && L == a, in_b = on && L == b;
+    ax += in_a ? r : 0.0, ay += in_a ? 1.0 : 0.0;
+    bx += in_b ? r : 0.0, by += in_b ? 1.0 : 0.0;
+    if (__ballot(in_b) && !__ballot(in_a)) {
+      std::swap(a, b);
+      std::swap(ax, bx), std::swap(ay, by);
+    }
+    bool alone = on && !in_a && !in_b;
+    int largest = 1, next = -1;
+    for (uint64_t left = __ballot(alone); left;) {
+      const int M = __builtin_amdgcn_readlane(L, __ffsll((unsigned long long)left) - 1);
+      const uint64_t same = __ballot(L == M);
+      left &= ~same;
+      if (__popcll(same) > largest) largest = __popcll(same), next = M;
+    }
+    if (next >= 0) {
+      if (a >= 0) {
+        if (b >= 0) give(b, bx, by);
+        b = next, bx = L == next ? r : 0.0, by = L == next ? 1.0 : 0.0;
+      } else {
+        a = next, ax = L == next ? r : 0.0, ay = L == next ? 1.0 : 0.0;
+      }
+      alone = alone && L != next;
+    }
+    for (uint64_t left = largest >= kManyLanes ? __ballot(alone) : 0; left;) {
+      const int M = __builtin_amdgcn_readlane(L, __ffsll((unsigned long long)left) - 1);
+      const uint64_t same = __ballot(L == M);
+      left &= ~same;
+      if (__popcll(same) < kManyLanes) continue;
+      give(M, L == M ? r : 0.0, L == M ? 1.0 : 0.0);
+      alone = alone && L != M;
+    }
+    if (alone) add_sums(acc, L, r, 1.0);
+  }
+  if (b >= 0) give(b, bx, by);
+  wave_sum2(ax, ay);
+  if (lane == 0) {
+    label_s[wv] = a;
+    sum_s[wv][0] = ax;
+    sum_s[wv][1] = ay;
   }
   __syncthreads();
-  if (threadIdx.x != 0) return;
-  for (int w = 0; w < kBlock / 64; ++w) {  // wavefronts of one component are added together
-    const int L = label_s[w];
-    if (L < 0) continue;
-    double a = 0.0, c = 0.0;
-    for (int v = w; v < kBlock / 64; ++v)
-      if (label_s[v] == L) {
-        a += sum_s[v][0];
-        c += sum_s[v][1];
-        if (v > w) label_s[v] = -1;
-      }
-    unsafeAtomicAdd(acc + 2 * (int64_t)L, a);
-    unsafeAtomicAdd(acc + 2 * (int64_t)L + 1, c);
+  if (wv != 0) return;
+  // lane w holds wavefront w's sums; those of one component are added together
+  a = lane < kWaves ? label_s[lane] : -1;
+  ax = lane < kWaves ? sum_s[lane][0] : 0.0;
+  ay = lane < kWaves ? sum_s[lane][1] : 0.0;
+  for (uint64_t left = __ballot(a >= 0); left;) {
+    const int M = __builtin_amdgcn_readlane(a, __ffsll((unsigned long long)left) - 1);
+    left &= ~__ballot(a == M);
+    give(M, a == M ? ax : 0.0, a == M ? ay : 0.0);
   }
 }
 
@@ -314,7 +335,8 @@ extern "C" int lbm_project_invariants(int32_t q, const int32_t shape[3], uint32_
   double *acc = scratch;
   double *ra = scratch + sums, *rb = ra + 3 * n;
   hipLaunchKernelGGL(k_clear, dim3(clear_grid), dim3(kBlock), 0, s, acc, sums);
-  hipLaunchKernelGGL(k_mass, dim3(std::min<unsigned>(grid, kMassBlocks)), dim3(kBlock), 0, s, n, labels, count,
+  const int64_t mass_blocks = std::min<int64_t>((n + kMassThreads - 1) / kMassThreads, kMassBlocks);
+  hipLaunchKernelGGL(k_mass, dim3((unsigned)mass_blocks), dim3(kMassThreads), 0, s, n, labels, count,
                      (const double *)rho, acc);
   hipLaunchKernelGGL(k_rescale, dim3(grid), dim3(kBlock), 0, s, n, labels, count, (const double *)acc, rho0, rho);
   const Lattice3 g{shape[0], shape[1], shape[2], periodic};
