@@ -162,16 +162,22 @@ constexpr int kTwoCopy = kPhaseTwoCopy, kAAGather = kPhaseAAGather, kAALocal = k
 // with the slowest wavefront, and the way through LDS makes each one longer:
 // it stores directly (few_tiles).  48^3 spheres (up to 1,728 tiles), without / with:
 // FP64 6.6 / 6.8, FP32 6.0 / 6.2; 64^3 (4,096): FP64 11.7 / 11.3, FP32 7.2 /
-// 7.6; 80^3 (8,000): 19.0 / 18.2 and 11.7 / 11.5.
+// 7.6; 80^3 (8,000): 19.0 / 18.2 and 11.7 / 11.5.  From a list, four samples of 24^3:
+// FP64 5.8 / 6.2, FP32 5.5 / 5.8.  The persistent grid gains less: four of 16^3 (256
+// tiles) FP64 6.5 / 6.9, FP32 6.0 / 6.3, but four of 32^3 (2,048) FP64 10.9 / 10.5.
 template <int S, int PH, bool MRT, bool STAGE = true>
 constexpr int stage_bytes() {
   return STAGE && PH != kPhaseAAGather && (S == LBM_F64 || (S == LBM_F32_OFFSET && !MRT))
              ? 64 * 19 * (int)sizeof(typename Store<S>::T)
              : 0;
 }
+
+// Which tiles a launch visits.
+enum { kDirect = 0, kList = 1, kPersistent = 2 };
+
 template <int S>
-bool few_tiles(int64_t waves) {  // two wavefronts per SIMD of FP64, four of FP32
-  return waves <= (S == LBM_F64 ? 2048 : 4096);
+bool few_tiles(int64_t waves, int mode) {  // two wavefronts per SIMD of FP64, four of FP32
+  return waves <= (S != LBM_F64 ? 4096 : mode == kPersistent ? 512 : 2048);
 }
 
 // The nodes of one 4x4x4 tile: gather, collide, store (into `stage`, where
@@ -440,14 +446,11 @@ __device__ __forceinline__ void step19_tile(int64_t tile, in_ptr<PH, void> src, 
   }
 }
 
-// Which tiles a launch visits; kFew: kDirect, stored directly (few_tiles).
-enum { kDirect = 0, kList = 1, kPersistent = 2, kFew = 3 };
-
 // kDirect: wavefront w updates tile w.  kList: wavefront w updates tile
 // list[w] if w < *count.  kPersistent: a fixed grid of G wavefronts strides
 // over list[0 .. *count).  The count lives in device memory, so a captured
 // graph stays valid when the active set changes.
-template <int S, int WPB, bool NT, bool INC, int PH, bool MRT, int MODE, bool SH>
+template <int S, int WPB, bool NT, bool INC, int PH, bool MRT, int MODE, bool SH, bool STAGE>
 __global__ void __launch_bounds__(64 * WPB)
     k_step19(in_ptr<PH, void> src, out_ptr<PH, void> dst, TileArgs a, const NbRec *__restrict__ nrec,
              const uint32_t *__restrict__ nrow, const uint32_t *__restrict__ rbase,
@@ -455,7 +458,6 @@ __global__ void __launch_bounds__(64 * WPB)
              const int32_t *__restrict__ count) {
   extern __shared__ __attribute__((aligned(16))) char stage_lds[];
   const int wv = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
-  constexpr bool STAGE = MODE != kFew;
   char *stage = stage_lds + wv * stage_bytes<S, PH, MRT, STAGE>();
   // XCD assignment, chosen per form by measurement: chunks of 8 blocks for
   // the two-copy FP64/FP32 step (BGK and MRT), 16 for the FP64 BGK single
@@ -466,7 +468,7 @@ __global__ void __launch_bounds__(64 * WPB)
                                              : (S == LBM_F64 && !MRT ? 16 : 0);
   const int64_t blk = kChunk ? xcd_chunk(blockIdx.x, gridDim.x, kChunk) : xcd_remap(blockIdx.x, gridDim.x);
   const int64_t gw = blk * WPB + wv;
-  if constexpr (MODE == kDirect || MODE == kFew) {
+  if constexpr (MODE == kDirect) {
     if (gw >= a.n_waves) return;
     step19_tile<S, NT, INC, PH, MRT, SH, STAGE>(gw, src, dst, a, nrec, nrow, rbase, coef, stage);
   } else if constexpr (MODE == kList) {
@@ -553,14 +555,18 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
     };
     auto by_mode = [&](auto nt) {
       constexpr bool NT = decltype(nt)::value;
-      constexpr int lds = W * stage_bytes<S, PH, MRT>();
-      if constexpr (lds != 0)
-        if (mode == kDirect && few_tiles<S>(a.n_waves)) return go(k_step19<S, W, NT, INC, PH, MRT, kFew, SH>, 0);
-      switch (mode) {
-        case kDirect: return go(k_step19<S, W, NT, INC, PH, MRT, kDirect, SH>, lds);
-        case kList: return go(k_step19<S, W, NT, INC, PH, MRT, kList, SH>, lds);
-        default: return go(k_step19<S, W, NT, INC, PH, MRT, kPersistent, SH>, lds);
-      }
+      auto staged = [&](auto st) {
+        constexpr bool STAGE = decltype(st)::value;
+        constexpr int lds = W * stage_bytes<S, PH, MRT, STAGE>();
+        switch (mode) {
+          case kDirect: return go(k_step19<S, W, NT, INC, PH, MRT, kDirect, SH, STAGE>, lds);
+          case kList: return go(k_step19<S, W, NT, INC, PH, MRT, kList, SH, STAGE>, lds);
+          default: return go(k_step19<S, W, NT, INC, PH, MRT, kPersistent, SH, STAGE>, lds);
+        }
+      };
+      if constexpr (stage_bytes<S, PH, MRT>() != 0)
+        if (!few_tiles<S>(a.n_waves, mode)) return staged(BC<true>{});
+      return staged(BC<false>{});
     };
     // MRT is built with non-temporal stores only (the planner rejects others)
     if constexpr (MRT) return by_mode(BC<true>{});
@@ -579,7 +585,7 @@ hipError_t step19_persistent_blocks(const Variant &v, bool single_copy, bool shu
       constexpr int S = decltype(sc)::value, W = decltype(wc)::value, PH = decltype(pc)::value;
       constexpr bool INC = decltype(ic)::value, MRT = decltype(mc)::value, SH = decltype(hc)::value;
       constexpr int lds = W * stage_bytes<S, PH, MRT>();
-      auto kern = k_step19<S, W, true, INC, PH, MRT, kPersistent, SH>;
+      auto kern = k_step19<S, W, true, INC, PH, MRT, kPersistent, SH, stage_bytes<S, PH, MRT>() != 0>;
       int k = 0;
       hipError_t r = allow_lds(reinterpret_cast<const void *>(kern), lds);
       if (r == hipSuccess) r = hipOccupancyMaxActiveBlocksPerMultiprocessor(&k, kern, 64 * W, lds);
