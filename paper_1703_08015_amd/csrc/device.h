@@ -569,6 +569,24 @@ __device__ __forceinline__ BgkRate<L, R> bgk_rate(R om, R gx, R gy, R gz) {
   return k;
 }
 
+// One scalar register (pair) for a value that is the same in every lane.
+__device__ __forceinline__ void to_scalar(float &v) {
+  v = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
+}
+__device__ __forceinline__ void to_scalar(double &v) {
+  const uint64_t b = __builtin_bit_cast(uint64_t, v);
+  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
+  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
+  v = __builtin_bit_cast(double, lo | hi << 32);
+}
+
+template <class L, class R>
+__device__ __forceinline__ BgkRate<L, R> uniform(BgkRate<L, R> k) {
+  to_scalar(k.om), to_scalar(k.h3);
+  static_for<L::Q / 2>([&](auto I) { to_scalar(k.odd[decltype(I)::value]), to_scalar(k.even[decltype(I)::value]); });
+  return k;
+}
+
 // BGK collision, Eqs. (2), (3) or (4), (7) with the Guo source, in place on f
 // (the PDFs, or their offsets), by pairs of opposite directions:
 //   poly = 9/2 (c.u)^2 - 3/2 u.u +- 3 c.u,   feq = w_i rho (1 + poly) or w_i (c0 + m poly),

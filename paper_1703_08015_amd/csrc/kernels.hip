@@ -77,11 +77,16 @@ __device__ __forceinline__ int lane_rank(uint64_t m) {
 }
 
 // ---- fused step -----------------------------------------------------------------
-// The two-copy D2Q9 BGK step asks for 8 waves per SIMD: left to itself the
-// compiler clusters the loads of a 16x16 tile into 76 VGPRs (6 waves), where
-// 56 registers with no extra instructions give all 8 (+5% measured; the
-// single-copy phases measured slower with 8 and keep the compiler's choice).  Runs
-// of two-copy D2Q9 steps go to step9.hip where that is faster.
+// The two-copy D2Q9 BGK step asks for 8 waves per SIMD (60-62 registers in FP64;
+// with the separate collision of before, left to itself, the compiler clustered
+// the loads of a 16x16 tile into 76 registers, 6 waves, 5% slower; the
+// single-copy phases measured slower with 8 and keep the compiler's choice).
+// Runs of two-copy D2Q9 steps go to step9.hip where that is faster.  What the
+// collision takes from the rate and the force alone is the same for a
+// wavefront's nodes and kept in scalar registers: in vector registers the FP64
+// incompressible D3Q19 gather needs 144 (3 waves; 124 and 4 so: 96^3 30.2 ->
+// 28.6 us per single-copy step, 4x4x8 tiles), the FP64 D2Q9 local step 68 (7; 60
+// and 8 so).
 template <class L, int AX, int AY, int AZ, int S, int WPB, bool INC, int PH, bool MRT>
 __global__ void __launch_bounds__(64 * WPB)
     __attribute__((amdgpu_waves_per_eu(L::Q == 9 && !MRT && PH == kPhaseTwoCopy ? 8 : 1)))
@@ -169,7 +174,7 @@ __global__ void __launch_bounds__(64 * WPB)
   if constexpr (MRT)
     collide_mrt<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, gx, gy, gz, a.mrt);  // Eq. (8)
   else
-    collide_bgk<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, bgk_rate<L>((R)omega_d, gx, gy, gz));
+    collide_bgk<L, S, INC>(f, sum, jx, jy, jz, (R)a.rho0, uniform(bgk_rate<L>((R)omega_d, gx, gy, gz)));
   static_for<Q>([&](auto I) { put(I, f[decltype(I)::value]); });
 }
 

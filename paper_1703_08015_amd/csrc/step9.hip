@@ -38,17 +38,6 @@ struct Window {
   int steps, wx;  // steps of this launch; windows along x
 };
 
-// One scalar register (pair) for a value that is the same in every lane.
-__device__ __forceinline__ void to_scalar(float &v) {
-  v = __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, v)));
-}
-__device__ __forceinline__ void to_scalar(double &v) {
-  const uint64_t b = __builtin_bit_cast(uint64_t, v);
-  const uint64_t lo = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)b);
-  const uint64_t hi = (uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)(b >> 32));
-  v = __builtin_bit_cast(double, lo | hi << 32);
-}
-
 template <int S, bool INC, bool MRT>
 __global__ void __launch_bounds__(kThreads, (S == LBM_F64 && MRT ? 4 : 8))
     k_steps9(const void *__restrict__ src_, void *__restrict__ dst_, TileArgs a, const int32_t *__restrict__ tmap,
@@ -106,9 +95,7 @@ __global__ void __launch_bounds__(kThreads, (S == LBM_F64 && MRT ? 4 : 8))
     if (i > 0 && open_s[at - L::C[i][0] - kPitch * L::C[i][1]]) open |= 1u << i;
   });
   const R gx = (R)a.samples[0].g[0], gy = (R)a.samples[0].g[1], gz = (R)a.samples[0].g[2];
-  BgkRate<L, R> rate = bgk_rate<L>((R)omega, gx, gy, gz);
-  to_scalar(rate.om), to_scalar(rate.h3);
-  static_for<Q / 2>([&](auto I) { to_scalar(rate.odd[decltype(I)::value]), to_scalar(rate.even[decltype(I)::value]); });
+  const BgkRate<L, R> rate = uniform(bgk_rate<L>((R)omega, gx, gy, gz));
   for (int t = 0; t < w.steps; ++t) {
     if (fluid)
       static_for<Q - 1>([&](auto I) {

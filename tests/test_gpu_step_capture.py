@@ -1,6 +1,6 @@
 """Steps captured by the caller: an even number of steps ends in the copy it
-starts from, so the caller's graph can be replayed, whatever number of
-launches the steps take."""
+starts from, so the caller's graph can be replayed, with steps outside it in
+between, whatever number of launches the steps take."""
 import numpy as np
 import pytest
 
@@ -27,11 +27,12 @@ def test_replays_of_a_callers_graph(shape, tile, storage, pattern, steps):
     graph = torch.cuda.CUDAGraph()
     with torch.cuda.graph(graph, stream=side):
         run.step(steps)
-    for _ in range(3):
+    for k in range(4):
         with torch.cuda.stream(side):
             graph.replay()
+            run.step(4 * k)  # an even number of steps of its own between the replays
         side.synchronize()
-        for _ in range(steps):
+        for _ in range(steps + 4 * k):
             one.step()
         torch.cuda.synchronize()
         with torch.cuda.stream(side):
