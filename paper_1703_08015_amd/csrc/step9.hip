@@ -13,17 +13,16 @@
 // What bounds it: vector arithmetic at two workgroups per compute unit (FP64: one thread
 // per node, 64 registers) and, where a window's nodes are read, HBM: 1.78 reads
 // and one write of each PDF per four steps.  What is the same for all nodes is
-// kept in scalar registers: without that FP64 needs 82 vector registers, runs
-// one workgroup per compute unit and spills if it is held to 64 (35.0 and 42.4
-// against 29.1 us per step on the 1536x1500 channel with discs, with a shorter
-// collision than the one of now).
-// Per step, k_step before -> this: that channel 39.7 -> 33.1 us (FP64), 27.2 ->
-// 20.8 (FP32); 4096x4096: 418 -> 279 and 248 -> 159; 512x512: 8.0 -> 5.0 and
-// 6.1 -> 3.4; 256x256: 4.5 -> 2.3 and 4.2 -> 1.8; 64x64: 4.3 -> 2.1 and 4.2 ->
-// 1.7, MRT 4.4 -> 2.8 and 4.3 -> 2.3 (eight steps per launch in the last two).
+// kept in scalar registers (uniform()): without that FP64 needs 82 vector
+// registers, runs one workgroup per compute unit and spills if it is held to 64
+// (a fifth to nearly a half slower on the 1536x1500 channel with discs).
+// Per step, k_step before -> this: that channel 39.7 -> 33.3 us (FP64), 27.2 ->
+// 21.0 (FP32); the sweep over sizes and steps per launch stands at steps9_launches.
 //
 // Steps of other forms (one PDF copy, a lid, FP16 storage, which rounds every
 // step to 16 bits, batches) and single steps run k_step (kernels.hip).
+#include <algorithm>
+
 #include "device.h"
 #include "kernels.h"
 
@@ -31,6 +30,7 @@ namespace lbm {
 namespace {
 
 constexpr int kWin = 32, kThreads = kWin * kWin;   // window edge, threads
+constexpr int kMostSteps = 10;                     // per launch
 constexpr int kPitch = kWin + 2, kArea = kPitch * kPitch;  // with a guard ring
 
 struct Window {
@@ -131,41 +131,62 @@ int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * 
 
 }  // namespace
 
-// Launches for n steps (n: single steps).  Eight steps per launch where the
-// windows of eight steps are no more than the compute units, so that all run
-// at once and a step costs its latency; else four, where the doubled layers
-// weigh less.  One sweep over the steps per launch, FP64, us per step:
-//   256x256: 4.4 by one, 2.7 by four, 2.0 by eight;
-//   512x512: 7.5 by one, 4.5 by four, 5.4 by five, 5.5 by eight;
-//   4096x4096: 416 by one, 326 by two, 253 by four, 255 by five, 316 by eight.
+// Launches for n steps (n: single steps).
+//
+// Where the windows of four steps are no more than the compute units, all run
+// at once and a launch costs its latency: as many steps per launch as leave it
+// so, ten at most.  Else four, where the doubled layers weigh less.  One sweep
+// over the steps per launch, us per step by 1, 2, 3, 4, 5, 6, 8, 10:
+//   64x64      FP64  4.0  4.3  3.4  2.8  2.6  2.4  2.1  2.0
+//              FP32  3.9  3.9  2.9  2.2  2.1  1.9  1.7  1.6
+//   256x256    FP64  4.3  4.6  3.5  3.0  2.7  2.5  2.2  3.2   (256 windows by 8, 484 by 10)
+//              FP32  4.1  4.0  3.0  2.3  2.3  2.0  1.7  2.4
+//   320x320    FP64  5.1  4.7  3.6  3.1  2.8  2.5  3.4  4.6   (256 by 6, 324 by 7)
+//   384x384    FP64  5.9  4.8  3.7  3.0  4.1  3.8  5.0  5.9   (256 by 4, 324 by 5)
+//   512x512    FP64  7.3  7.6  5.9  4.9  6.1  5.7  6.4  11
+//              FP32  5.8  5.8  4.1  3.4  4.5  4.1  4.5  7.7
+//   1500x1536  FP64  36.4 37.3 34.3 32.8 34.8 38.2 53   86
+//              FP32  25.4 27.4 22.8 20.7 22.8 25.2 35   57
+//   4096x4096  FP64  303  312  281  267  266  279  376  623
+//              FP32  214  223  173  150  166  180  249  417
+// so FP32 takes the same numbers as FP64, and launches of two steps alone do not pay.
+// MRT, whose FP64 form does not fit 64 registers, gains on small grids only:
+//   64x64      FP64  4.3  4.8  3.9  3.4  3.2  3.0  2.7  2.6
+//   384x384    FP64  6.2  5.3  4.3  3.7  6.1  5.8  7.8  9.9
+//   1500x1536  FP64  40.2 52.1 49.2 48.9;  FP32  27.7 35.0 31.2 29.6
+//
 // The launches are as many as n modulo 2, so that n steps leave the state in
 // the copy where n single steps leave it: a caller that captured an even
-// number of steps replays them from the copy they end in.  The steps are
-// spread evenly over them (ten steps by four: 3 + 3 + 2 + 2).  Single steps
-// stay for
-//  - two steps of FP32 on larger grids (1536x1500: 25.5 us per step by two,
-//    24.7 by one),
-//  - MRT on larger grids, whose FP64 form does not fit 64 registers (1536x1500:
-//    FP64 41.7 us by one, 49.0 by four; FP32 28.0 and 28.4),
-//  - geometries with fewer than one tile for every four windows, where most of
-//    a launch would look at solid nodes.
+// number of steps replays them from the copy they end in.  Where that asks for
+// one launch more or less, the larger grids take what puts fewer steps into
+// launches of five or three (50 steps: two of five and ten of four).
+//
+// Single steps stay for geometries with fewer than one tile for every four
+// windows, where most of a launch would look at solid nodes, and where the grid
+// would not fit a launch.
 int steps9_launches(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
-  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1) return n;
-  const bool small = (int64_t)windows(shape[0], 8) * windows(shape[1], 8) <= 256;
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || n < 3) return n;
+  auto grid = [&](int k) { return (int64_t)windows(shape[0], k) * windows(shape[1], k); };
+  constexpr int kUnits = 256;
+  const bool small = grid(4) <= kUnits;
   if (!small && v.collision == LBM_COLLISION_MRT) return n;
-  const int most = small ? 8 : 4;
+  int most = 4;
+  while (small && most < kMostSteps && grid(most + 1) <= kUnits) ++most;
   int launches = n / most + (n % most != 0);
-  launches += (launches ^ n) & 1;
+  if ((launches ^ n) & 1) {
+    const int fives = n - 4 * (launches - 1), threes = 4 * (launches + 1) - n;  // launches of so many steps
+    launches += !small && fives <= launches - 1 && 5 * fives < 3 * threes ? -1 : 1;
+  }
   const int k = n / launches + (n % launches != 0);
-  if (k == 1 || (!small && k == 2 && v.storage != LBM_F64)) return n;
-  return (int64_t)windows(shape[0], k) * windows(shape[1], k) <= n_waves ? launches : n;
+  const int64_t blocks = grid(k);
+  return k > 2 && blocks <= n_waves && blocks * kThreads <= (int64_t)UINT32_MAX ? launches : n;
 }
 
 hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const TileArgs &a, const MeshArgs &m,
                          const int32_t shape[3], const int32_t tgrid[3], uint32_t periodic, int steps, double omega,
                          hipStream_t s) {
   if (a.n_waves == 0) return hipSuccess;
-  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || steps < 1 || steps > 8 || src == dst) return hipErrorInvalidValue;
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || steps < 1 || steps > kMostSteps || src == dst) return hipErrorInvalidValue;
   Window w{shape[0], shape[1], tgrid[0], (int)periodic, steps, windows(shape[0], steps)};
   const unsigned blocks = (unsigned)((int64_t)w.wx * windows(shape[1], steps));
   auto go = [&](auto sc, auto ic, auto mc) -> hipError_t {
