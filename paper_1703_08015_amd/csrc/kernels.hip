@@ -496,6 +496,24 @@ __global__ void __launch_bounds__(256) k_export_tiles(const void *src, TileArgs 
   });
 }
 
+template <class L, int AX, int AY, int AZ, int S>
+__global__ void __launch_bounds__(256) k_import_tiles(void *dst_, TileArgs a, const double *dense) {
+  using St = Store<S>;
+  const int64_t gw = wave_of_grid();
+  if (gw >= a.n_waves) return;
+  const NodeCtx<AX, AY, AZ> c = node_ctx<AX, AY, AZ>(a, gw);
+  if (!c.fluid) return;
+  const SampleRec &s = a.samples[c.sample];
+  typename St::T *dst = static_cast<typename St::T *>(dst_);
+  const double *in = dense + L::Q * s.dense0 + c.loc;
+  static_for<L::Q>([&](auto I) {
+    constexpr int i = decltype(I)::value;
+    const double v = in[i * s.n_nodes];
+    const double val = St::offset ? v - L::Wt[i] * a.rho0 : v;
+    St::store(dst, set_entry<L, AX, AY, AZ, i>(a, c), (typename St::R)val, a.f16_scale);
+  });
+}
+
 // (Four neighbouring tiles' rows of one line are read by one workgroup.)
 template <class L, int AX, int AY, int AZ, int S>
 __global__ void __launch_bounds__(256)
@@ -765,6 +783,20 @@ static int64_t group_parts(const Variant &v, int64_t groups) { return groups * (
 // 248 us over all groups, 425 us filled first).
 static bool fill_first(const MeshArgs &m) { return 2 * m.n_listed <= m.n_groups; }
 
+// Whether a workgroup per group would be more threads than a launch can have
+// (lattices of 2^32 nodes); a wavefront per stored tile may still fit.
+static bool too_many(const Variant &v, int64_t groups) { return group_parts(v, groups) * 256 > (int64_t)UINT32_MAX; }
+
+// Whether every listed group of four places holds one tile, as on a lattice of
+// at most four nodes in x: three of a workgroup's wavefronts would have nothing
+// to read.  256x256x4 (4,096 tiles) in FP64, by groups / by tiles: import 14.4 /
+// 11.0 us, export 23.7 / 19.4 (with its fill; of 256 tiles 4.7 / 7.8, so from 2,048
+// on), moments 10.0 / 12.4; with two tiles a group import 21.9 / 20.3, export
+// 25.1 / 31.6.
+static bool single_tiles(const Variant &v, const TileArgs &a, const MeshArgs &m) {
+  return v.ax == 4 && a.n_waves == m.n_listed * (v.az / 4);
+}
+
 // Zeroes n doubles: 16-byte stores, four per thread, over a grid that covers
 // them (the first and last value by themselves where they are not aligned).
 __global__ void __launch_bounds__(256) k_zero(double *p, int64_t n) {
@@ -789,7 +821,7 @@ static hipError_t zero(double *p, int64_t n, hipStream_t s) {
 
 hipError_t launch_moments(const Variant &v, const void *src, const TileArgs &a, const MeshArgs &m, double *rho,
                           double *u, hipStream_t s) {
-  const bool fill = fill_first(m);
+  const bool fill = fill_first(m) || too_many(v, m.n_groups);
   if (fill) {
     hipError_t e = zero(rho, m.dense_nodes, s);
     if (e == hipSuccess) e = zero(u, 3 * m.dense_nodes, s);
@@ -808,7 +840,7 @@ hipError_t launch_moments(const Variant &v, const void *src, const TileArgs &a, 
 
 hipError_t launch_export(const Variant &v, const void *src, const TileArgs &a, const MeshArgs &m, double *dense,
                          hipStream_t s) {
-  const bool fill = fill_first(m);
+  const bool fill = fill_first(m) || too_many(v, m.n_groups) || (single_tiles(v, a, m) && m.n_listed >= 2048);
   if (fill) {
     const hipError_t e = zero(dense, v.q * m.dense_nodes, s);
     if (e != hipSuccess || a.n_waves == 0) return e;
@@ -829,7 +861,11 @@ hipError_t launch_import(const Variant &v, void *dst, const TileArgs &a, const M
   const int64_t n = group_parts(v, m.n_listed);
   if (n == 0) return hipSuccess;
   return dispatch(aux(v), [&]<class L, int AX, int AY, int AZ, int S, int WPB>() {
-    hipLaunchKernelGGL((k_import<L, AX, AY, AZ, S>), dim3((unsigned)n), dim3(256), 0, s, dst, a, m, m.groups, dense);
+    if (single_tiles(v, a, m) || too_many(v, m.n_listed))
+      hipLaunchKernelGGL((k_import_tiles<L, AX, AY, AZ, S>), dim3(blocks_for(a.n_waves, 4)), dim3(256), 0, s, dst, a,
+                         dense);
+    else
+      hipLaunchKernelGGL((k_import<L, AX, AY, AZ, S>), dim3((unsigned)n), dim3(256), 0, s, dst, a, m, m.groups, dense);
     return hipGetLastError();
   });
 }
