@@ -181,7 +181,7 @@ __device__ __forceinline__ double kept(double momentum, double r) {
 __device__ __forceinline__ double times(int count, double r) { return count != 0 ? count * r : 0.0; }
 
 template <class L, int ENDS>
-__global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t *lab, int32_t count,
+__global__ void __launch_bounds__(kBlock) k_link_sweep(int64_t first, Lattice3 g, const int32_t *lab, int32_t count,
                                                        const double *rho, double *u, const double *r_in,
                                                        double *r_out) {
   __shared__ double rs[3][kHaloNodes];
@@ -189,8 +189,8 @@ __global__ void __launch_bounds__(kBlock) k_link_sweep(Lattice3 g, const int32_t
   const int64_t n = (int64_t)g.nx * g.ny * g.nz;
   const int tid = threadIdx.x;
   const int bx = (g.nx + kSx - 1) / kSx, by = (g.ny + kSy - 1) / kSy;
-  const int ox = (int)(blockIdx.x % bx) * kSx, oy = (int)(blockIdx.x / bx % by) * kSy,
-            oz = (int)(blockIdx.x / ((unsigned)bx * by)) * kSz;
+  const int64_t brick = first + blockIdx.x;
+  const int ox = (int)(brick % bx) * kSx, oy = (int)(brick / bx % by) * kSy, oz = (int)(brick / bx / by) * kSz;
   if (tid < kHy * kHz) open[tid] = 0;
   __syncthreads();
   for (int e = tid; e < kHaloNodes; e += kBlock) {
@@ -294,19 +294,24 @@ void launch_sweeps(int64_t n, Lattice3 g, const int32_t *labels, int32_t count, 
                    double *ra, double *rb, int iterations, hipStream_t s) {
   const int64_t bricks =
       (int64_t)((g.nx + kSx - 1) / kSx) * ((g.ny + kSy - 1) / kSy) * ((g.nz + kSz - 1) / kSz);
-  const dim3 grid((unsigned)bricks), block(kBlock);
-  hipLaunchKernelGGL((k_link_sweep<L, kFirst>), grid, block, 0, s, g, labels, count, rho, u, (const double *)nullptr,
-                     ra);
+  auto sweep = [&](auto ends, const double *r_in, double *r_out) {
+    // as many launches as threads per launch ask for (flat lattices of 2^31 nodes: two)
+    constexpr int64_t most = UINT32_MAX / kBlock;
+    for (int64_t first = 0; first < bricks; first += most)
+      hipLaunchKernelGGL((k_link_sweep<L, decltype(ends)::value>), dim3((unsigned)std::min(most, bricks - first)),
+                         dim3(kBlock), 0, s, first, g, labels, count, rho, u, r_in, r_out);
+  };
+  sweep(std::integral_constant<int, kFirst>{}, nullptr, ra);
   if (iterations == 1) {
-    hipLaunchKernelGGL(k_velocity, dim3((unsigned)((n + kBlock - 1) / kBlock)), block, 0, s, n, labels, count, rho,
-                       (const double *)ra, u);
+    hipLaunchKernelGGL(k_velocity, dim3((unsigned)((n + kBlock - 1) / kBlock)), dim3(kBlock), 0, s, n, labels, count,
+                       rho, (const double *)ra, u);
     return;
   }
   for (int it = 1; it + 1 < iterations; ++it) {
-    hipLaunchKernelGGL((k_link_sweep<L, kInner>), grid, block, 0, s, g, labels, count, rho, u, (const double *)ra, rb);
+    sweep(std::integral_constant<int, kInner>{}, ra, rb);
     std::swap(ra, rb);
   }
-  hipLaunchKernelGGL((k_link_sweep<L, kLast>), grid, block, 0, s, g, labels, count, rho, u, (const double *)ra, rb);
+  sweep(std::integral_constant<int, kLast>{}, ra, rb);
 }
 
 }  // namespace
