@@ -414,29 +414,27 @@ constexpr double mrt_src_C(int k, int a, int b) {
 
 template <class L, int K, class R>
 __device__ __forceinline__ R mrt_source_moment(R m, const R (&u)[3], const R (&g)[3], R ug) {
-  // explicit fma and no other contraction, as in collide_mrt
-#pragma clang fp contract(off)
   R acc = R(0);
   bool any = false;
-  auto add = [&](R c, R v) {
-    acc = any ? std::fma(c, v, acc) : c * v;
+  auto add = [&](R term) {
+    acc = any ? acc + term : term;
     any = true;
   };
   static_for<3>([&](auto A) {
     constexpr int a = decltype(A)::value;
     constexpr double ca = 3.0 * mrt_src_A<L>(K, a);
-    if constexpr (ca != 0.0) add(R(ca), g[a]);
+    if constexpr (ca != 0.0) add(R(ca) * g[a]);
   });
   {
     constexpr double cb = -3.0 * mrt_src_B<L>(K);
-    if constexpr (cb != 0.0) add(R(cb), ug);
+    if constexpr (cb != 0.0) add(R(cb) * ug);
   }
   static_for<3>([&](auto A) {
     constexpr int a = decltype(A)::value;
     static_for<3>([&](auto B) {
       constexpr int b = decltype(B)::value;
       constexpr double cc = 9.0 * mrt_src_C<L>(K, a, b);
-      if constexpr (cc != 0.0) add(R(cc), u[a] * g[b]);
+      if constexpr (cc != 0.0) add(R(cc) * (u[a] * g[b]));
     });
   });
   return any ? m * acc : R(0);
@@ -445,10 +443,13 @@ __device__ __forceinline__ R mrt_source_moment(R m, const R (&u)[3], const R (&g
 template <class L, int S, bool INC, class R>
 __device__ __forceinline__ void collide_mrt(R (&f)[L::Q], R sum, R jx, R jy, R jz, R rho0, R gx, R gy, R gz,
                                             const MrtRates &mr) {
-  // Every multiply-add is an explicit fma and nothing else is contracted, so
-  // each kernel variant (phase, launch mode) rounds the same way and the
-  // single-copy steps stay bit-identical to the two-copy step.  sum and j
-  // are plain sums of the gathered values.
+  // Every multiply-add here is an explicit fma and nothing else is contracted,
+  // so each kernel variant (phase, launch mode, several D2Q9 steps at once)
+  // rounds the same way and the single-copy steps stay bit-identical to the
+  // two-copy step.  sum and j are plain sums of the gathered values.  Only the
+  // moments of the source (mrt_source_moment) are sums of products that the
+  // compiler contracts; it does so alike in all of these kernels, which
+  // tests/test_gpu_mrt_bits.py holds.
 #pragma clang fp contract(off)
   constexpr int Q = L::Q;
   constexpr bool off = Store<S>::offset;
