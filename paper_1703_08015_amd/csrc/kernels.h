@@ -49,8 +49,14 @@ hipError_t launch_step19(const Variant &v, int phase, bool shuffle, const void *
 // phases when single_copy).
 hipError_t step19_persistent_blocks(const Variant &v, bool single_copy, bool shuffle, int64_t *blocks);
 // Several two-copy D2Q9 steps of one sample without a lid in one launch
-// (step9.hip); steps9_launches: launches for n steps (n: single steps).
-int steps9_launches(const Variant &v, const int32_t shape[3], int64_t n_waves, int n);
+// (step9.hip).  steps9_runs: how n steps are launched, as runs of launches of
+// so many steps each (1: launch_step).
+struct StepRuns {
+  struct {
+    int steps, launches;
+  } run[3];
+};
+StepRuns steps9_runs(const Variant &v, const int32_t shape[3], int64_t n_waves, int n);
 hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const TileArgs &a, const MeshArgs &m,
                          const int32_t shape[3], const int32_t tgrid[3], uint32_t periodic, int steps, double omega,
                          hipStream_t s);

@@ -727,14 +727,14 @@ extern "C" int lbm_init(lbm_solver *s, const double *rho, const double *u) {
   return LBM_OK;
 }
 
-// Launches for n > 0 steps, as many as n modulo 2.
-static int step_launches(const lbm_solver *s, int n) {
-  if (s->single_copy || s->n_samples != 1 || (s->args.lid.axis >= 0 && s->n_lid_tiles > 0)) return n;
-  return lbm::steps9_launches(s->var, s->samples_h[0].shape, s->args.n_waves, n);
+// How n steps are launched; the launches are as many as n modulo 2.
+static lbm::StepRuns step_runs(const lbm_solver *s, int n) {
+  if (s->single_copy || s->n_samples != 1 || (s->args.lid.axis >= 0 && s->n_lid_tiles > 0))
+    return {{{1, n}, {0, 0}, {0, 0}}};
+  return lbm::steps9_runs(s->var, s->samples_h[0].shape, s->args.n_waves, n);
 }
 
-// Enqueue one launch of k steps (1, unless step_launches asked for fewer
-// launches) from copy (two copies) or layout (single copy) `from` on `st`.  The
+// Enqueue one launch of k steps (1, unless step_runs says more) from copy (two copies) or layout (single copy) `from` on `st`.  The
 // state is then in the other copy (layout).
 static hipError_t enqueue_step(lbm_solver *s, int from, int k, hipStream_t st) {
   const int phase = !s->single_copy ? lbm::kPhaseTwoCopy : (from == 0 ? lbm::kPhaseAAGather : lbm::kPhaseAALocal);
@@ -764,13 +764,11 @@ static int capture(lbm_solver *s, int from) {
   HIP_TRY(hipStreamBeginCapture(s->cap_stream, hipStreamCaptureModeThreadLocal));
   hipError_t e = hipSuccess;
   int c = from;
-  int n = s->p.graph_steps;
-  for (int left = step_launches(s, n); left > 0 && e == hipSuccess; --left) {
-    const int k = n / left + (n % left != 0);
-    e = enqueue_step(s, c, k, s->cap_stream);
-    c ^= 1;
-    n -= k;
-  }
+  for (const auto &run : step_runs(s, s->p.graph_steps).run)
+    for (int k = 0; k < run.launches && e == hipSuccess; ++k) {
+      e = enqueue_step(s, c, run.steps, s->cap_stream);
+      c ^= 1;
+    }
   hipGraph_t g = nullptr;
   const hipError_t e2 = hipStreamEndCapture(s->cap_stream, &g);
   if (e == hipSuccess) e = e2;
@@ -797,13 +795,12 @@ extern "C" int lbm_step(lbm_solver *s, int32_t n) {
       n -= K;
     }
   }
-  for (int left = n > 0 ? step_launches(s, n) : 0; left > 0; --left) {
-    const int k = n / left + (n % left != 0);
-    HIP_TRY(enqueue_step(s, s->cur, k, s->stream));
-    s->cur ^= 1;
-    s->steps += k;
-    n -= k;
-  }
+  for (const auto &run : step_runs(s, n).run)
+    for (int k = 0; k < run.launches; ++k) {
+      HIP_TRY(enqueue_step(s, s->cur, run.steps, s->stream));
+      s->cur ^= 1;
+      s->steps += run.steps;
+    }
   return LBM_OK;
 }
 

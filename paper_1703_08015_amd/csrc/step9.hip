@@ -17,7 +17,7 @@
 // registers, runs one workgroup per compute unit and spills if it is held to 64
 // (a fifth to nearly a half slower on the 1536x1500 channel with discs).
 // Per step, k_step before -> this: that channel 39.7 -> 33.3 us (FP64), 27.2 ->
-// 21.0 (FP32); the sweep over sizes and steps per launch stands at steps9_launches.
+// 21.0 (FP32); the sweep over sizes and steps per launch stands at steps9_runs.
 //
 // Steps of other forms (one PDF copy, a lid, FP16 storage, which rounds every
 // step to 16 bits, batches) and single steps run k_step (kernels.hip).
@@ -131,7 +131,7 @@ int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * 
 
 }  // namespace
 
-// Launches for n steps (n: single steps).
+// How n steps are launched.
 //
 // Where the windows of four steps are no more than the compute units, all run
 // at once and a launch costs its latency: as many steps per launch as leave it
@@ -157,29 +157,38 @@ int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * 
 //
 // The launches are as many as n modulo 2, so that n steps leave the state in
 // the copy where n single steps leave it: a caller that captured an even
-// number of steps replays them from the copy they end in.  Where that asks for
-// one launch more or less, the larger grids take what puts fewer steps into
-// launches of five or three (50 steps: two of five and ten of four).
+// number of steps replays them from the copy they end in.  A launch of an odd
+// number of steps keeps to that by itself, one of an even number comes with
+// another: `most` steps in pairs of launches (if it is even), then for the rest
+// one or two launches and one or two single steps (50 steps by four: twelve
+// launches and two single steps, 32.9 us per step at 1536x1500 FP64; spread
+// evenly over fourteen launches 33.3).
 //
-// Single steps stay for geometries with fewer than one tile for every four
+// Single steps alone stay for geometries with fewer than one tile for every four
 // windows, where most of a launch would look at solid nodes, and where the grid
 // would not fit a launch.
-int steps9_launches(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
-  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || n < 3) return n;
+StepRuns steps9_runs(const Variant &v, const int32_t shape[3], int64_t n_waves, int n) {
+  const StepRuns single{{{1, n}, {0, 0}, {0, 0}}};
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || n < 3) return single;
   auto grid = [&](int k) { return (int64_t)windows(shape[0], k) * windows(shape[1], k); };
   constexpr int kUnits = 256;
   const bool small = grid(4) <= kUnits;
-  if (!small && v.collision == LBM_COLLISION_MRT) return n;
+  if (!small && v.collision == LBM_COLLISION_MRT) return single;
   int most = 4;
   while (small && most < kMostSteps && grid(most + 1) <= kUnits) ++most;
-  int launches = n / most + (n % most != 0);
-  if ((launches ^ n) & 1) {
-    const int fives = n - 4 * (launches - 1), threes = 4 * (launches + 1) - n;  // launches of so many steps
-    launches += !small && fives <= launches - 1 && 5 * fives < 3 * threes ? -1 : 1;
-  }
-  const int k = n / launches + (n % launches != 0);
-  const int64_t blocks = grid(k);
-  return k > 2 && blocks <= n_waves && blocks * kThreads <= (int64_t)UINT32_MAX ? launches : n;
+  const int pair = most % 2 ? 1 : 2, full = n / (pair * most) * pair, r = n - full * most;
+  StepRuns p{{{most, full}, {0, 0}, {1, r}}};
+  auto rest = [&](int steps, int launches) {
+    p.run[1] = {steps, launches};
+    p.run[2].launches = r - steps * launches;
+  };
+  if (r > most + 1 && r / 2 >= 3)
+    rest(r / 2, 2);  // (and a single step if r is odd)
+  else if (r >= 3)
+    rest(r % 2 ? std::min(r, most - (most % 2 ? 0 : 1)) : r - 1, 1);  // odd
+  const int64_t blocks = grid(full ? most : p.run[1].steps);
+  return p.run[0].launches + p.run[1].launches > 0 && blocks <= n_waves && blocks * kThreads <= (int64_t)UINT32_MAX
+             ? p : single;
 }
 
 hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const TileArgs &a, const MeshArgs &m,
