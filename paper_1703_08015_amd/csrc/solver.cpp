@@ -734,8 +734,9 @@ static lbm::StepRuns step_runs(const lbm_solver *s, int n) {
   return lbm::steps9_runs(s->var, s->samples_h[0].shape, s->args.n_waves, n);
 }
 
-// Enqueue one launch of k steps (1, unless step_runs says more) from copy (two copies) or layout (single copy) `from` on `st`.  The
-// state is then in the other copy (layout).
+// Enqueue one launch of k steps (1, unless step_runs says more) from copy (two
+// copies) or layout (single copy) `from` on `st`.  The state is then in the
+// other copy (layout).
 static hipError_t enqueue_step(lbm_solver *s, int from, int k, hipStream_t st) {
   const int phase = !s->single_copy ? lbm::kPhaseTwoCopy : (from == 0 ? lbm::kPhaseAAGather : lbm::kPhaseAALocal);
   if (k > 1) {

@@ -175,7 +175,7 @@ StepRuns steps9_runs(const Variant &v, const int32_t shape[3], int64_t n_waves, 
   const bool small = grid(4) <= kUnits;
   if (!small && v.collision == LBM_COLLISION_MRT) return single;
   int most = 4;
-  while (small && most < kMostSteps && grid(most + 1) <= kUnits) ++most;
+  while (small && most < kMostSteps && grid(most + 1) <= std::min<int64_t>(kUnits, n_waves)) ++most;
   const int pair = most % 2 ? 1 : 2, full = n / (pair * most) * pair, r = n - full * most;
   StepRuns p{{{most, full}, {0, 0}, {1, r}}};
   auto rest = [&](int steps, int launches) {

@@ -48,3 +48,13 @@ def test_most_steps(shape, periodic, storage, model, collision):
     assert torch.cuda.is_available()
     m = np.random.default_rng(shape[1]).random(shape) < 0.25
     _compare(torch, m, periodic, (4, 9, 10, 19, 20, 30), storage, model, collision)
+
+
+@pytest.mark.parametrize("tiles", [2, 4, 6, 12])
+def test_few_tiles_on_a_small_grid(tiles):
+    """192x192 with tiles**2 of 144 tiles stored: as many steps per launch as there are wavefronts for windows."""
+    import torch
+    assert torch.cuda.is_available()
+    m = np.ones((1, 192, 192), bool)
+    m[0, :16 * tiles, :16 * tiles] = np.random.default_rng(tiles).random((16 * tiles, 16 * tiles)) < 0.2
+    _compare(torch, m, 0, (10, 17, 20), "f64")
