@@ -84,16 +84,24 @@ def traffic_for(kernel_name, workload_key):
         return None
     note = "recorded %s in profiles/traffic.json from rocprofv3 FETCH_SIZE and WRITE_SIZE runs of the same kernel " \
            "source (L2 misses, including those the MALL serves: an upper bound on HBM bytes)" % rec.get("date", "")
-    return rec.get("bytes_per_launch"), note
+    return rec.get("bytes_per_step", rec.get("bytes_per_launch")), note
+
+
+def several_steps(args):
+    """Whether the D2Q9 channel's steps run several per launch (k_steps9): two FP64 or FP32 copies, at least three
+    steps, MRT on small grids only."""
+    return (args.geometry == "channel2d" and args.pattern == "two-copy" and args.storage != "f16" and
+            args.steps >= 3 and (args.collision == "bgk" or args.n <= 384))
 
 
 def step_kernel_key(args):
     """Name of the timed step kernel and the workload key of its traffic record."""
     inc = args.model == "incompressible"
     if args.geometry == "channel2d":
-        kernel = "k_step<D2Q9,16x16,%s%s%s%s>" % (args.storage, ",incompressible" if inc else "",
-                                                  ",single-copy" if args.pattern == "single-copy" else "",
-                                                  ",mrt" if args.collision == "mrt" else "")
+        kernel = "%s<D2Q9,16x16,%s%s%s%s>" % ("k_steps9" if several_steps(args) else "k_step", args.storage,
+                                              ",incompressible" if inc else "",
+                                              ",single-copy" if args.pattern == "single-copy" else "",
+                                              ",mrt" if args.collision == "mrt" else "")
         return kernel, "%s_%d_%s_generic_%s" % (args.geometry, args.n, args.storage, args.order)
     kernel = "%s<D3Q19,4x4x4,%s%s%s%s%s>" % ("k_step" if args.kernel == "generic" else "k_step19", args.storage,
                                              ",shuffle" if args.kernel == "shuffle" else "",
@@ -145,17 +153,23 @@ def record_traffic(args, argv):
     fk, wk = values(fetch_dir, csv_name), values(write_dir, csv_name)
     if not fk or not wk:
         raise SystemExit("no %s dispatches in the counter runs" % csv_name)
-    fb = sum(fk) / len(fk) * 1024 * f_scale
-    wb = sum(wk) / len(wk) * 1024 * w_scale
+    per = "launch"
+    if csv_name == "k_steps9":  # launches of several steps: what one step moves
+        if args.warmup >= 3:
+            raise SystemExit("record the runs of steps with --warmup 2 (which is stepped singly)")
+        per = "step"
+    fb = sum(fk) / (args.steps if per == "step" else len(fk)) * 1024 * f_scale
+    wb = sum(wk) / (args.steps if per == "step" else len(wk)) * 1024 * w_scale
     generic = args.kernel == "generic" or args.geometry == "channel2d"
-    files = ["paper_1703_08015_amd/csrc/%s" % ("kernels.hip" if generic else "step19.hip"),
+    files = ["paper_1703_08015_amd/csrc/%s" % ("step9.hip" if per == "step" else
+                                               "kernels.hip" if generic else "step19.hip"),
              "paper_1703_08015_amd/csrc/device.h"]
     src = b"".join(open(os.path.join(ROOT, f), "rb").read() for f in files)
     cmd = " ".join(["python3", "bench.py"] + argv)
     path = os.path.join(ROOT, "profiles", "traffic.json")
     table = json.load(open(path)) if os.path.exists(path) else {}
     table.setdefault(kernel, {})[wkey] = {
-        "bytes_per_launch": int(round(fb + wb)), "fetch_bytes": int(round(fb)), "write_bytes": int(round(wb)),
+        "bytes_per_" + per: int(round(fb + wb)), "fetch_bytes": int(round(fb)), "write_bytes": int(round(wb)),
         "fetch_scale": round(f_scale, 5), "write_scale": round(w_scale, 5),
         "fetch_kib_per_dispatch_raw": round(sum(fk) / len(fk), 1),
         "write_kib_per_dispatch_raw": round(sum(wk) / len(wk), 1),
@@ -163,7 +177,8 @@ def record_traffic(args, argv):
         "source_sha256": hashlib.sha256(src).hexdigest(), "source_files": files,
         "date": time.strftime("%Y-%m-%d", time.gmtime(os.path.getmtime(os.path.join(fetch_dir,
                                                                                  "run_counter_collection.csv")))),
-        "commands": ["rocprofv3 --pmc %s -T -d %s -o run --output-format csv -- %s" % (c, d, cmd)
+        "commands": ["rocprofv3 --pmc %s -T -d %s -o run --output-format csv -- %s"
+                     % (c, os.path.basename(os.path.normpath(d)), cmd)
                      for c, d in (("FETCH_SIZE", fetch_dir), ("WRITE_SIZE", write_dir))]}
     with open(path, "w") as fh:
         json.dump(table, fh, indent=1)
@@ -688,7 +703,8 @@ def main():
     nf = info["n_fluid"]
     sd = SD[args.storage]
     mlups = nf * args.steps / wall / 1e6
-    alg_bytes = nf * 2 * q * sd  # Eq. (10) per non-solid node, per launch
+    # Eq. (10) per non-solid node and step (a launch of several D2Q9 steps moves less)
+    alg_bytes = nf * 2 * q * sd
     achieved = alg_bytes / (launch_ms * 1e-3) / 1e9
     # D3Q19 on 4x4x4 tiles runs the scalar-mask kernel unless the generic one is asked for
     kernel, wkey = step_kernel_key(args)
