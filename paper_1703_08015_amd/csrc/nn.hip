@@ -1590,7 +1590,7 @@ struct DistBrick {
 // Bricks of an axis: n split into pieces of nearly equal length, at least half
 // of B where there is more than one (so that a halo of 4 ends in the next: B is
 // at least 8 then).
-__device__ __host__ __forceinline__ int dist_bricks(int n, int B) { return (n + B - 1) / B; }
+__device__ __host__ __forceinline__ int dist_bricks(int n, int B) { return (n - 1) / B + 1; }
 __device__ __forceinline__ int dist_begin(int b, int n, int B) {
   const int nb = dist_bricks(n, B), rem = n % nb;
   return b * (n / nb) + (b < rem ? b : rem);

@@ -127,7 +127,7 @@ __global__ void __launch_bounds__(kThreads, (S == LBM_F64 && MRT ? 4 : 8))
     });
 }
 
-int windows(int n, int steps) { return (n + kWin - 2 * steps - 1) / (kWin - 2 * steps); }
+int windows(int n, int steps) { return (n - 1) / (kWin - 2 * steps) + 1; }
 
 }  // namespace
 
@@ -195,7 +195,8 @@ hipError_t launch_steps9(const Variant &v, const void *src, void *dst, const Til
                          const int32_t shape[3], const int32_t tgrid[3], uint32_t periodic, int steps, double omega,
                          hipStream_t s) {
   if (a.n_waves == 0) return hipSuccess;
-  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || steps < 1 || steps > kMostSteps || src == dst) return hipErrorInvalidValue;
+  if (v.q != 9 || v.storage == LBM_F16_OFFSET || shape[2] != 1 || steps < 1 || steps > kMostSteps || src == dst)
+    return hipErrorInvalidValue;
   Window w{shape[0], shape[1], tgrid[0], (int)periodic, steps, windows(shape[0], steps)};
   const unsigned blocks = (unsigned)((int64_t)w.wx * windows(shape[1], steps));
   auto go = [&](auto sc, auto ic, auto mc) -> hipError_t {
